@@ -104,8 +104,8 @@ typedef struct {
     int64_t row_offset, n_rows;  /* rows of this geometry inside a data vector */
     int64_t col_offset, n_cols;  /* columns inside a coefficient vector       */
     int64_t rays_per_order[8];
-    int32_t apply_variant;       /* kernel variant used by op_apply            */
-    int32_t adjoint_variant;     /* kernel variant used by op_apply_adjoint    */
+    int32_t apply_variant;       /* kernel variant used by op_apply and        */
+    int32_t adjoint_variant;     /* op_apply_adjoint (unpinned: on one vector) */
     uint64_t digest;             /* FNV-1a hash of the grid and device tables  */
 } rtt_member_info;
 

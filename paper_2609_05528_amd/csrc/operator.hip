@@ -1128,6 +1128,8 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
         const int64_t ri = r0 + j;
         rc[j] = load_const_rec(a.rec + __builtin_amdgcn_readfirstlane((int)(ri < a.n_rays ? ri : r0)));
     }
+    // every product and sum is written as the fused operation it is, so that each form (wide or narrow
+    // stores, staged rows, one launch for many members) gives the same bits
     float xv[NB][2][4];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -1164,8 +1166,9 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
     for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int it = 0; it < 2; ++it)
-            zs[j][lane + it * WAVE] = rc[j].b00 * xv[j][it][0] + rc[j].b10 * xv[j][it][1] +
-                                      rc[j].b01 * xv[j][it][2] + rc[j].b11 * xv[j][it][3];
+            zs[j][lane + it * WAVE] =
+                fmaf(rc[j].b11, xv[j][it][3],
+                     fmaf(rc[j].b01, xv[j][it][2], fmaf(rc[j].b10, xv[j][it][1], rc[j].b00 * xv[j][it][0])));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1188,7 +1191,7 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
                 const int k0 = rc[j].k0;
                 for (int q = lane; q < F; q += WAVE) {
                     const float za = zat(k0 + q), zb = zat(k0 + q + 1);
-                    ob[pad + j * F + q] = za + th * (zb - za);
+                    ob[pad + j * F + q] = fmaf(th, zb - za, za);
                 }
             }
             range_store<NB>(ob, pad, NB * F, yb);
@@ -1213,10 +1216,10 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
                     const float z0 = zat(k0 + f), z1 = zat(k0 + f + 1), z2 = zat(k0 + f + 2);
                     const float z3 = zat(k0 + f + 3), z4 = zat(k0 + f + 4);
                     f4 v;
-                    v[0] = z0 + th * (z1 - z0);
-                    v[1] = z1 + th * (z2 - z1);
-                    v[2] = z2 + th * (z3 - z2);
-                    v[3] = z3 + th * (z4 - z3);
+                    v[0] = fmaf(th, z1 - z0, z0);
+                    v[1] = fmaf(th, z2 - z1, z1);
+                    v[2] = fmaf(th, z3 - z2, z2);
+                    v[3] = fmaf(th, z4 - z3, z3);
                     if (o) __builtin_nontemporal_store(v, (f4*)(yr + f));
                 }
             }
@@ -1237,8 +1240,8 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
             for (int f = 2 * lane; f < F; f += 2 * WAVE) {
                 const float z0 = zat(k0 + f), z1 = zat(k0 + f + 1), z2 = zat(k0 + f + 2);
                 f2 v;
-                v[0] = z0 + th * (z1 - z0);
-                v[1] = z1 + th * (z2 - z1);
+                v[0] = fmaf(th, z1 - z0, z0);
+                v[1] = fmaf(th, z2 - z1, z1);
                 __builtin_nontemporal_store(v, (f2*)(yr + f));
             }
         } else if (VEC4) {
@@ -1250,10 +1253,10 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
                 const float a1 = c1 ? z1 : z0, b1 = c1 ? z2 : z1;
                 const float a3 = c1 ? z2 : z1, b3 = c1 ? z3 : z2;
                 f4 v;
-                v[0] = z0 + th * (z1 - z0);
-                v[1] = a1 + th1 * (b1 - a1);
-                v[2] = z1 + th * (z2 - z1);
-                v[3] = a3 + th1 * (b3 - a3);
+                v[0] = fmaf(th, z1 - z0, z0);
+                v[1] = fmaf(th1, b1 - a1, a1);
+                v[2] = fmaf(th, z2 - z1, z1);
+                v[3] = fmaf(th1, b3 - a3, a3);
                 __builtin_nontemporal_store(v, (f4*)(yr + 4 * g));
             }
         } else {
@@ -1270,7 +1273,7 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
                     t = odd ? (c1 ? th - 0.5f : th + 0.5f) : th;
                 }
                 const float za = zat(k0 + jz), zb = zat(k0 + jz + 1);
-                __builtin_nontemporal_store(za + t * (zb - za), yr + q);
+                __builtin_nontemporal_store(fmaf(t, zb - za, za), yr + q);
             }
         }
     }
@@ -2557,6 +2560,7 @@ static const AdjVariant kAdjVariants[] = {
     {"rows4", 4, 4, 0},      {"rows8", 4, 8, 0},      {"visit2v", 3, 2, 0},    {"visit4v", 3, 4, 0},
     {"visitd", 3, 1, 1},     {"visitd2v", 3, 2, 1},   {"visitd4v", 3, 4, 1},   {"visitp2v", 3, 2, 2},
     {"visitp4v", 3, 4, 2},   {"visitb", 3, 1, 3},     {"visitb2v", 3, 2, 3},
+    {"visitc", 5, 0, 0},
 };
 constexpr int kNumAdj = sizeof(kAdjVariants) / sizeof(kAdjVariants[0]);
 
@@ -2620,12 +2624,48 @@ static int reg_lpr(int64_t F)
     return best;
 }
 
-int default_adjoint_variant(const Member& m)
+// The variant of a member that neither geometry_set_variant nor geometry_tune has pinned.  Which
+// arithmetic a handle uses (the lean or the absolute-hat products, the row sweeps or the base cells)
+// depends on the geometry alone, never on the number of vectors, so a vector gets the same bits alone and
+// inside a block, and in every launch mode; the forms of one arithmetic are chosen by the call's size.
+int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
 {
-    if (visit_supported(m)) return 11;
-    return 2;
+    if (m.apply_variant >= 0) return m.apply_variant;
+    if (!lean_supported(m)) return m.P <= m.Q ? 2 : 1;
+    const int64_t F = m.grid.n_frames;
+    if (m.grid.n_hat <= ABS_KMAX) {
+        // Absolute hats.  Rows that end inside a 128-byte line leave staged and aligned when they are long
+        // enough to outweigh the lost gather reuse (60 vectors, 12 geometries of 64 x 64 cells: 134, 143
+        // and 151 frames 297, 138 and 394 us row-ordered against 370, 175 and 599; 125 frames 83 against
+        // 79, 160 frames 195 against 144).  One launch for all members serves one or two vectors (12
+        // geometries: 59 against 71 us; 8 vectors 438 against 366).
+        if (g->members.size() > 1 && nvec <= 2) return 11;
+        return m.Q == 1 && F >= 130 && F % 32 != 0 && F <= lean_fcmax(1) ? 14 : 11;
+    }
+    // More than 128 hats: the lean products; records in data-row order where rows share lines with their
+    // neighbours (200^2 x 150 frames, 64 vectors: 310 against 365 us; 360^2 x 300, 8 vectors: 285 against
+    // 347; 256^2 x 192, whole lines: 168 against 157) or steps are half hats, unless the coefficient
+    // blocks outgrow the last cache (512^2 x 512, 4 vectors: 271 against 297 us; 16: 1418 against 1205).
+    const bool rows = m.Q == 2 ? 4 * m.n_cols * nvec <= ((int64_t)128 << 20) : F % 32 != 0;
+    return rows ? 13 : 4;
 }
-int default_apply_variant(const Member& m) { return lean_supported(m) ? 4 : (m.P <= m.Q ? 2 : 1); }
+int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
+{
+    if (m.adj_variant >= 0) return m.adj_variant;
+    if (!visit_supported(m)) return 2;
+    // Several geometries: the row sweep, which has a form for all members in one launch (12 geometries of
+    // 2 to 12 rays a cell: 60 vectors 2.15 ms against 2.54 ms for base cells member by member; 8 vectors 460
+    // against 394 us; one vector without row pairs 170 against 227 us with them).
+    if (g->members.size() > 1) return nvec >= 4 ? 19 : 16;
+    // One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
+    // 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
+    // 240 against 248), which need even, aligned rows at half steps.
+    const int64_t cells = (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
+    if (2 * m.n_rays >= 9 * cells && (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m)) return 23;
+    // the row sweep: row pairs (which fall back to single rows for few tasks), or four vectors per wave
+    // for middle blocks on grids of many rows (64 x 64 cells, 16 vectors: 34 against 43 us)
+    return nvec >= 8 && nvec < 32 && m.grid.n_r >= 64 ? 18 : nvec > 1 ? 19 : 16;
+}
 
 template <int TP, int TQ, int NB, int ZI>
 static void apply_batch_launch(const ApplyArgs& a, int nvec, hipStream_t s)
@@ -2741,7 +2781,7 @@ int launch_apply(const rtt_geometry* g, const Member& m, const float* x, float* 
                  int64_t x_stride, int64_t y_stride, uint32_t mask, hipStream_t s, int variant)
 {
     if (m.n_rays == 0 || nvec == 0) return RTT_OK;
-    if (variant < 0 || variant >= n_apply_variants()) variant = m.apply_variant;
+    if (variant < 0 || variant >= n_apply_variants()) variant = apply_variant_for(g, m, nvec);
     if (!apply_variant_ok(m, variant)) variant = m.P <= m.Q ? 2 : 1;
     if (variant == 8 || variant == 9) {
         StripArgs sa;
@@ -2885,7 +2925,6 @@ int launch_apply(const rtt_geometry* g, const Member& m, const float* x, float* 
     a.x_stride = x_stride;
     a.y_stride = y_stride;
     a.mask = mask;
-    if (variant < 0 || variant >= n_apply_variants()) variant = m.apply_variant;
     if (m.P == 1 && m.Q == 1) apply_dispatch<1, 1>(a, nvec, variant, s);
     else if (m.P == 1 && m.Q == 2) apply_dispatch<1, 2>(a, nvec, variant, s);
     else apply_dispatch<0, 0>(a, nvec, variant, s);
@@ -3116,11 +3155,11 @@ static bool apply_multi_reg(const rtt_geometry* g, int b, int e, const float* x,
                             hipStream_t s, bool persist, bool shared, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
-    const int v0 = m0.apply_variant;
+    const int v0 = apply_variant_for(g, m0, nvec);
     bool vec4 = (((uintptr_t)y) & 15) == 0 && (nvec == 1 || (g->n_rows % 4) == 0);
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
-        if (!lean_supported(m) || m.Q != m0.Q || m.apply_variant != v0) return false;
+        if (!lean_supported(m) || m.Q != m0.Q || apply_variant_for(g, m, nvec) != v0) return false;
         vec4 = vec4 && (m.grid.n_frames % 4) == 0 && (m.row_offset % 4) == 0;
     }
     const int NI = v0 == 6 ? 1 : 2;
@@ -3186,23 +3225,26 @@ static bool apply_multi(const rtt_geometry* g, int b, int e, const float* x, flo
                         hipStream_t s, bool persist, bool shared, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
-    if (m0.apply_variant == 6 || m0.apply_variant == 7)
+    const int v0 = apply_variant_for(g, m0, nvec);
+    if (v0 == 6 || v0 == 7)
         return apply_multi_reg(g, b, e, x, y, nvec, mask, s, persist, shared, rc, probe);
     // wide output stores (8-byte aligned rows at Q = 1, 16-byte at Q = 2), decided per member
     const int wa = m0.Q == 1 ? 2 : 4;
     const bool vec4 = (((uintptr_t)y) & (4 * wa - 1)) == 0 && (nvec == 1 || (g->n_rows % wa) == 0);
-    bool all8 = true, use_abs = m0.apply_variant == 11;
+    bool all8 = true, use_abs = v0 == 11;
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
+        const int vi = apply_variant_for(g, m, nvec);
+        if (m.apply_variant < 0 && nvec > 2) return false;   // unpinned members: see apply_variant_for
         if (use_abs) {
-            if (!apply_variant_ok(m, 11) || m.Q != m0.Q || m.apply_variant != 11) return false;
+            if (!apply_variant_ok(m, 11) || m.Q != m0.Q || vi != 11) return false;
             continue;
         }
         if (!lean_supported(m) || m.Q != m0.Q) return false;
-        if (m0.apply_variant == 13 ? m.apply_variant != 13 : (m.apply_variant != 4 && m.apply_variant != 5)) return false;
-        all8 = all8 && m.apply_variant == 5;
+        if (v0 == 13 ? vi != 13 : (vi != 4 && vi != 5)) return false;
+        all8 = all8 && vi == 5;
     }
-    const FwdRec* recs = m0.apply_variant == 13 ? g->d_fwd_row : g->d_fwd;
+    const FwdRec* recs = v0 == 13 ? g->d_fwd_row : g->d_fwd;
     const int NB = all8 && !use_abs ? 8 : 4;
     LeanMulti a;
     a.G = e - b;
@@ -3344,19 +3386,20 @@ static bool adjoint_multi(const rtt_geometry* g, int b, int e, const float* y, f
                           hipStream_t s, bool persist, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
+    const int v0 = adjoint_variant_for(g, m0, nvec);
     bool pair = (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (g->n_rows % 2) == 0);
     int64_t wide = 0;
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
-        if (!visit_supported(m) || m.Q != m0.Q || m.adj_variant != m0.adj_variant ||
-            (m0.adj_variant != 11 && m0.adj_variant != 16 && m0.adj_variant != 19 && m0.adj_variant != 20))
+        if (!visit_supported(m) || m.Q != m0.Q || adjoint_variant_for(g, m, nvec) != v0 ||
+            (v0 != 11 && v0 != 16 && v0 != 19 && v0 != 20))
             return false;
         pair = pair && (m.grid.n_frames % 2) == 0 && (m.row_offset % 2) == 0;
         wide += (int64_t)m.grid.n_r * m.nseg[0] * nvec;
     }
     // row pairs (lane-shifted taps; frame pairs at Q = 2) read visit set 2
-    const bool rp = (m0.adj_variant == 19 || m0.adj_variant == 20) && (m0.Q == 1 || pair);
-    if (m0.adj_variant == 20 && !rp) return false;
+    const bool rp = (v0 == 19 || v0 == 20) && (m0.Q == 1 || pair);
+    if (v0 == 20 && !rp) return false;
     const int set = rp ? 2 : wide >= 16384 ? 0 : 1;
     // task count with the narrowest hat chunk (62 hats, the largest count any V gives); every
     // member's blocks must fit the visit kernel's 31-bit buffer ranges
@@ -3394,16 +3437,16 @@ static bool adjoint_multi(const rtt_geometry* g, int b, int e, const float* y, f
     // row pairs: two (visitp2v) or four (visitp4v) vectors per wave, as in the single-geometry
     // launch, when the launch has that many and every member's group of vectors fits the buffer
     // ranges
-    int vpw = std::min(m0.adj_variant == 20 ? 4 : 2, nvec);
+    int vpw = std::min(v0 == 20 ? 4 : 2, nvec);
     if (vpw == 3) vpw = 2;
     for (int i = b; i < e; ++i)
         while (vpw > 1 && !visit_fits(g->members[i].n_rows, g->members[i].n_cols, g->n_rows, g->n_cols, vpw)) vpw /= 2;
     if (rp && m0.Q == 1) visit_multi_dispatch<1, false, true, 2>(a, g, b, e, set, nvec, persist, s, vpw);
     else if (rp) visit_multi_dispatch<2, true, true, 2>(a, g, b, e, set, nvec, persist, s, vpw);
-    else if (m0.Q == 1 && (m0.adj_variant == 16 || m0.adj_variant == 19))
+    else if (m0.Q == 1 && (v0 == 16 || v0 == 19))
         visit_multi_dispatch<1, false, true>(a, g, b, e, set, nvec, persist, s);
     else if (m0.Q == 1) visit_multi_dispatch<1, false>(a, g, b, e, set, nvec, persist, s);
-    else if (pair && (m0.adj_variant == 16 || m0.adj_variant == 19))
+    else if (pair && (v0 == 16 || v0 == 19))
         visit_multi_dispatch<2, true, true>(a, g, b, e, set, nvec, persist, s);
     else if (pair) visit_multi_dispatch<2, true>(a, g, b, e, set, nvec, persist, s);
     else visit_multi_dispatch<2, false>(a, g, b, e, set, nvec, persist, s);
@@ -3451,7 +3494,7 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
     a.y_stride = y_stride;
     a.x_stride = x_stride;
     a.mask = mask;
-    if (variant < 0 || variant >= n_adjoint_variants()) variant = m.adj_variant;
+    if (variant < 0 || variant >= n_adjoint_variants()) variant = adjoint_variant_for(g, m, nvec);
     if (!adjoint_variant_ok(m, variant)) variant = 2;
     if (variant == 12 || variant == 13) {
         RowsArgs ra;
@@ -3488,6 +3531,12 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
         }
         RTT_HIP(hipGetLastError());
         return RTT_OK;
+    }
+    // base cells: frame pairs at Q = 2; else the single-row lane-shifted form
+    if (variant == 23) {
+        const bool fpair = m.Q == 1 || ((m.grid.n_frames % 2) == 0 && (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (y_stride % 2) == 0));
+        if (fpair && adjoint_cells_ok(m)) return launch_adjoint_cells(g, m, y, x, nvec, y_stride, x_stride, mask, s);
+        variant = nvec >= 2 ? 17 : 16;
     }
     if ((variant == 11 || variant >= 14) && !visit_fits(m.n_rows, m.n_cols, y_stride, x_stride, 1)) variant = 2;
     // base rows (visit set 3): frame pairs at Q = 2; else the single-row lane-shifted form
@@ -3640,9 +3689,9 @@ int whole_operator_launches(const rtt_geometry* g, bool adjoint)
         for (int i = b; i < e; ++i) {
             const Member& m = g->members[i];
             if (m.n_rays == 0) continue;
-            // the base-row adjoint makes two passes (frame pairs at Q = 2; else the single-row form)
-            const bool br = adjoint && (m.adj_variant == 21 || m.adj_variant == 22) &&
-                            (m.Q == 1 || (m.grid.n_frames % 2) == 0);
+            // the base-row and base-cell adjoints make two passes (frame pairs at Q = 2; else the single-row form)
+            const int v = adjoint ? adjoint_variant_for(g, m, 1) : 0;
+            const bool br = adjoint && (v == 21 || v == 22 || v == 23) && (m.Q == 1 || (m.grid.n_frames % 2) == 0);
             n += br ? 2 : 1;
         }
     }

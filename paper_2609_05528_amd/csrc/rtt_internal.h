@@ -67,6 +67,7 @@ struct alignas(16) FwdRec {
     int32_t pad1;
 };
 static_assert(sizeof(FwdRec) == 48, "FwdRec must be 48 bytes");
+constexpr int FWD_PAD = 8;   // zero records past the end of the cell-sorted forward records (batched readers)
 
 // One geometry of a handle, as the kernels see it.
 struct Member {
@@ -78,8 +79,8 @@ struct Member {
     int64_t col_offset, n_cols;
     int64_t cell_begin;    // first CSR entry (n_cells + 1 entries)
     int64_t rays_per_order[8];
-    int32_t adj_variant;   // adjoint kernel variant (default heuristic or autotuner)
-    int32_t apply_variant; // forward kernel variant
+    int32_t adj_variant;   // pinned adjoint kernel variant (set or tuned); -1: chosen for each call
+    int32_t apply_variant; // pinned forward kernel variant, or -1
     uint64_t digest;       // FNV-1a of the grid and this member's device records
     // visit-list sets: [0] single rows, 16-column segments (many vectors per call); [1] single
     // rows, narrower segments chosen so one vector alone gives enough (row, segment) tasks;
@@ -146,12 +147,17 @@ int launch_apply(const rtt_geometry* g, const Member& m, const float* x, float* 
                  int64_t x_stride, int64_t y_stride, uint32_t mask, hipStream_t s, int variant);
 int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec,
                    int64_t y_stride, int64_t x_stride, uint32_t mask, hipStream_t s, int variant);
+// A^T over base cells (adjoint_cells.hip); data rows must be even and 8-byte aligned when Q = 2
+bool adjoint_cells_ok(const Member& m);
+int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec, int64_t y_stride,
+                         int64_t x_stride, uint32_t mask, hipStream_t s);
 int n_adjoint_variants();
 int n_apply_variants();
 const char* adjoint_variant_name(int v);
 const char* apply_variant_name(int v);
-int default_adjoint_variant(const Member& m);
-int default_apply_variant(const Member& m);
+// the variant a call on nvec vectors uses: the pinned one, or the one its sizes choose
+int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec);
+int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec);
 bool visit_supported(const Member& m);
 bool lean_supported(const Member& m);
 // forward / adjoint variant v can run on member m (ratio and size limits)

@@ -414,8 +414,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
         m.col_offset = col_off;
         row_off += m.n_rows;
         col_off += m.n_cols;
-        m.adj_variant = default_adjoint_variant(m);
-        m.apply_variant = default_apply_variant(m);
+        m.adj_variant = m.apply_variant = -1;
         m.digest = fnv1a(&g, sizeof(g));
         m.digest = fnv1a(gr.data(), gr.size() * sizeof(RayRec), m.digest);
     }
@@ -437,8 +436,10 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_visits, vb);
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_vtask, tb);
     const size_t fb = fwd.size() * sizeof(FwdRec);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd, fb);
+    const size_t fpad = FWD_PAD * sizeof(FwdRec);
+    if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd, fb + fpad);
     if (e == hipSuccess) e = hipMemcpy(h->d_fwd, fwd.data(), fb, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset((char*)h->d_fwd + fb, 0, fpad);
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd_row, fb);
     if (e == hipSuccess) e = hipMemcpy(h->d_fwd_row, fwd_row.data(), fb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_rays, recs.data(), rb, hipMemcpyHostToDevice);
@@ -459,7 +460,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
         delete h;
         return rc;
     }
-    h->table_bytes = (int64_t)(rb + cb + vb + tb + 2 * fb + sb);
+    h->table_bytes = (int64_t)(rb + cb + vb + tb + 2 * fb + fpad + sb);
     *out = h;
     return RTT_OK;
 }
@@ -510,8 +511,8 @@ extern "C" int geometry_member(const rtt_geometry* g, int32_t idx, rtt_member_in
     info->col_offset = m.col_offset;
     info->n_cols = m.n_cols;
     for (int n = 0; n < 8; ++n) info->rays_per_order[n] = m.rays_per_order[n];
-    info->apply_variant = m.apply_variant;
-    info->adjoint_variant = m.adj_variant;
+    info->apply_variant = apply_variant_for(g, m, 1);
+    info->adjoint_variant = adjoint_variant_for(g, m, 1);
     info->digest = m.digest;
     return RTT_OK;
 }
