@@ -12,9 +12,19 @@
 
 namespace rtt {
 
+// A device block of the library's scratch: taken from the idle blocks that earlier calls gave back, or
+// allocated.  Its contents are whatever its last user left.  dev_give waits for the device.
+struct DevBlock {
+    void* p = nullptr;
+    size_t cap = 0;
+    int dev = -1;
+};
+DevBlock dev_take(size_t bytes);
+void dev_give(const std::vector<DevBlock>& blocks);   // blocks of one device
+
 // Named, grow-only device scratch buffers owned by one driver call.
 struct Workspace {
-    std::map<std::string, std::pair<void*, size_t>> bufs;
+    std::map<std::string, DevBlock> bufs;
     void* get(const char* name, size_t bytes);
     void release();
     ~Workspace();

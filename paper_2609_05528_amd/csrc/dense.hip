@@ -30,6 +30,10 @@
 // MFMA operand layout used (32x32x2 f32): lane t supplies A[t%32][t/32] and
 // B[t/32][t%32]; accumulator register r of lane t holds
 // C[8(r/4) + 4(t/32) + r%4][t%32].
+#include <algorithm>
+#include <list>
+#include <mutex>
+
 #include "rtt_internal.h"
 #include "dense.h"
 
@@ -554,24 +558,137 @@ __global__ void k_scale_inv_sq(const double* __restrict__ Cd, const double* __re
 }
 
 // --------------------------------------------------------------------------------- host side
+// Idle device blocks of this library's scratch, kept between calls while a geometry handle is alive.
+// A driver call used to allocate its scratch and free it at its end: the two cost 2 to 4 ms of a 35 ms
+// rSVD on a fresh process and 110 ms of it (37 of 60 ms for a block Lanczos run) once the process had
+// allocated and returned tens of GB.  Blocks come back only after a device synchronisation (what hipFree
+// does too), so whoever takes one next, on any thread or stream, finds it unused.  At most POOL_IDLE_MAX
+// bytes per GPU stay idle, the longest idle leave first, all of them when an allocation fails or the
+// last geometry handle is freed.
+namespace {
+constexpr size_t POOL_IDLE_MAX = (size_t)8 << 30;
+struct IdleBlock {
+    void* p;
+    size_t cap;
+    int dev;
+};
+struct Pool {
+    std::mutex m;
+    std::list<IdleBlock> idle;   // longest idle first
+    int users = 0;               // live geometry handles
+};
+Pool& pool()
+{
+    static Pool* p = new Pool();   // never destroyed: the runtime may be gone before static destructors run
+    return *p;
+}
+// frees idle blocks of a device (or all) until at most `keep` bytes of it stay; the lock is held
+void pool_trim(Pool& q, int dev, size_t keep)
+{
+    size_t held = 0;
+    for (const IdleBlock& b : q.idle) held += (dev < 0 || b.dev == dev) ? b.cap : 0;
+    for (auto it = q.idle.begin(); it != q.idle.end() && held > keep;) {
+        if (dev >= 0 && it->dev != dev) {
+            ++it;
+            continue;
+        }
+        (void)hipFree(it->p);
+        held -= it->cap;
+        it = q.idle.erase(it);
+    }
+}
+}  // namespace
+
+void pool_user(int change)
+{
+    Pool& q = pool();
+    std::lock_guard<std::mutex> lock(q.m);
+    q.users += change;
+    if (q.users <= 0) pool_trim(q, -1, 0);
+}
+
+DevBlock dev_take(size_t bytes)
+{
+    // sizes in steps that let a later call of about the same size reuse the block
+    const size_t step = bytes >= ((size_t)1 << 20) ? (size_t)2 << 20 : 256;
+    const size_t want = std::max<size_t>(1, (bytes + step - 1) / step) * step;
+    DevBlock r;
+    if (hipGetDevice(&r.dev) != hipSuccess) return r;
+    Pool& q = pool();
+    {
+        std::lock_guard<std::mutex> lock(q.m);
+        auto best = q.idle.end();
+        for (auto it = q.idle.begin(); it != q.idle.end(); ++it)
+            if (it->dev == r.dev && it->cap >= want && it->cap <= want + want / 4 + 4096 &&
+                (best == q.idle.end() || it->cap < best->cap))
+                best = it;
+        if (best != q.idle.end()) {
+            r.p = best->p;
+            r.cap = best->cap;
+            q.idle.erase(best);
+            return r;
+        }
+    }
+    hipError_t e = hipMalloc(&r.p, want);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        {
+            std::lock_guard<std::mutex> lock(q.m);
+            pool_trim(q, r.dev, 0);
+        }
+        e = hipMalloc(&r.p, want);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        r.p = nullptr;
+        return r;
+    }
+    r.cap = want;
+    return r;
+}
+
+void dev_give(const std::vector<DevBlock>& blocks)
+{
+    int dev = -1, cur = -1;
+    for (const DevBlock& b : blocks)
+        if (b.p) dev = b.dev;
+    if (dev < 0) return;
+    (void)hipGetDevice(&cur);
+    if (cur != dev) (void)hipSetDevice(dev);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    Pool& q = pool();
+    {
+        std::lock_guard<std::mutex> lock(q.m);
+        for (const DevBlock& b : blocks) {
+            if (!b.p) continue;
+            if (idle && q.users > 0 && b.cap <= POOL_IDLE_MAX) q.idle.push_back({b.p, b.cap, b.dev});
+            else (void)hipFree(b.p);
+        }
+        pool_trim(q, dev, POOL_IDLE_MAX);
+    }
+    if (cur != dev) (void)hipSetDevice(cur);
+}
+
 Workspace::~Workspace() { release(); }
 void Workspace::release()
 {
-    for (auto& kv : bufs) hipFree(kv.second.first);
+    std::vector<DevBlock> all;
+    for (auto& kv : bufs) all.push_back(kv.second);
     bufs.clear();
+    dev_give(all);
 }
 void* Workspace::get(const char* name, size_t bytes)
 {
     auto it = bufs.find(name);
-    if (it != bufs.end() && it->second.second >= bytes) return it->second.first;
+    if (it != bufs.end() && it->second.cap >= bytes) return it->second.p;
     if (it != bufs.end()) {
-        hipFree(it->second.first);
+        dev_give({it->second});
         bufs.erase(it);
     }
-    void* p = nullptr;
-    if (hipMalloc(&p, bytes < 256 ? 256 : bytes) != hipSuccess) return nullptr;
-    bufs[name] = {p, bytes};
-    return p;
+    const DevBlock b = dev_take(bytes);
+    if (!b.p) return nullptr;
+    bufs[name] = b;
+    return b.p;
 }
 
 int gram(Workspace& ws, const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int64_t L,

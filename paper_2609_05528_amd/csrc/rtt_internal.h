@@ -100,6 +100,7 @@ struct Member {
 };
 
 struct Workspace;
+void pool_user(int change);   // a geometry handle is made (+1) or freed (-1): see the scratch pool in dense.hip
 
 }  // namespace rtt
 

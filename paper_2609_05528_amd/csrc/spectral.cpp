@@ -39,12 +39,17 @@ struct rtt_svd {
     float* U = nullptr;
     double* d_sigma = nullptr;          // device copy of sigma
     rtt::Workspace* ws = nullptr;       // grow-only scratch of tsvd_solve
+    std::vector<rtt::DevBlock> blocks;  // V, U and d_sigma
     ~rtt_svd()
     {
-        if (V) hipFree(V);
-        if (U) hipFree(U);
-        if (d_sigma) hipFree(d_sigma);
         delete ws;
+        dev_give(blocks);
+    }
+    // device memory that lives as long as the handle
+    void* take(size_t bytes)
+    {
+        blocks.push_back(dev_take(bytes));
+        return blocks.back().p;
     }
 };
 
@@ -220,8 +225,8 @@ int run_rsvd(Ctx& c, const rtt_svd_opts& o, const float* omega, rtt_svd* res)
     res->sets = sets;
     res->sigma.assign((size_t)sets * k, 0.0);
     res->resid.assign((size_t)sets * k, 0.0);
-    RTT_HIP(hipMalloc((void**)&res->V, sizeof(float) * (size_t)k * n));
-    if (o.keep_u) RTT_HIP(hipMalloc((void**)&res->U, sizeof(float) * (size_t)k * m));
+    if (!(res->V = (float*)res->take(sizeof(float) * (size_t)k * n))) return fail(RTT_ENOMEM, "right factors");
+    if (o.keep_u && !(res->U = (float*)res->take(sizeof(float) * (size_t)k * m))) return fail(RTT_ENOMEM, "left factors");
     // SVD of R^T (l x l leading block) of every set, the sets on host threads
     std::vector<std::vector<double>> Urs(sets), svs(sets), Ws(sets);
     host_for(sets, [&](int q) {
@@ -299,6 +304,8 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
     double* Cd = (double*)c.ws.get("lz_coef", sizeof(double) * (size_t)mdim * bp);
     if (!Vall || !Z || !Z2 || !W || !W2 || !Up || !Cd) return fail(RTT_ENOMEM, "Lanczos buffers");
     int rc;
+    // with an order mask A leaves the other orders' rows of W unwritten: they are zero in every left block
+    if (c.mask != 0 && ((rc = fill(W, (int64_t)b * m, 0.f, c.s)) || (rc = fill(Up, (int64_t)b * m, 0.f, c.s)))) return rc;
     if (start) RTT_HIP(hipMemcpyAsync(Z, start, sizeof(float) * b * n, hipMemcpyDeviceToDevice, c.s));
     else if ((rc = normal_fill(Z, (int64_t)b * n, o.seed, c.s))) return rc;
     std::vector<double> R, L, Rprev, T((size_t)mdim * mdim, 0.0), coef;
@@ -374,7 +381,7 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
         for (int jj = 0; jj < k; ++jj) Wk[(size_t)i * k + jj] = Wt[(size_t)i * mdim + jj];
     float* Cw = nullptr;
     if ((rc = upload_f32(c, "lz_w", Wk, Wk.size(), &Cw))) return rc;
-    RTT_HIP(hipMalloc((void**)&res->V, sizeof(float) * (size_t)k * n));
+    if (!(res->V = (float*)res->take(sizeof(float) * (size_t)k * n))) return fail(RTT_ENOMEM, "right factors");
     if ((rc = combine(Cw, mdim, k, Vall, n, res->V, n, n, 0.f, c.s))) return rc;
     RTT_HIP(hipStreamSynchronize(c.s));
     return RTT_OK;
@@ -429,7 +436,7 @@ extern "C" int rsvd(const rtt_geometry* g, const rtt_svd_opts* o, const float* o
         return fail(RTT_EINVAL, "rsvd: unknown method");
     }
     if (rc) return rc;
-    RTT_HIP(hipMalloc((void**)&res->d_sigma, sizeof(double) * res->sigma.size()));
+    if (!(res->d_sigma = (double*)res->take(sizeof(double) * res->sigma.size()))) return fail(RTT_ENOMEM, "singular values");
     RTT_HIP(hipMemcpy(res->d_sigma, res->sigma.data(), sizeof(double) * res->sigma.size(), hipMemcpyHostToDevice));
     *out = res.release();
     return RTT_OK;

@@ -461,6 +461,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
         return rc;
     }
     h->table_bytes = (int64_t)(rb + cb + vb + tb + 2 * fb + fpad + sb);
+    pool_user(1);
     *out = h;
     return RTT_OK;
 }
@@ -472,6 +473,7 @@ extern "C" int geometry_free(rtt_geometry* g)
     release_tables(g);
     g->magic = 0;
     delete g;
+    pool_user(-1);
     return RTT_OK;
 }
 
