@@ -10,77 +10,156 @@
 // changing) so that a whole solve can be captured into a graph.
 #include <algorithm>
 #include <cmath>
+#include <utility>
 #include <vector>
 
 #include "dense.h"
 
 namespace rtt {
 
-__global__ void k_axpy_lambda(float* __restrict__ Ap, const float* __restrict__ p, int64_t n, float lam)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t off = (int64_t)blockIdx.y * n;
-    if (i < n) Ap[off + i] += lam * p[off + i];
-}
+// The vector work of an iteration in three kernels (nine before: 20 iterations at 256^2, one right-hand
+// side, 1.44 -> 1.00 ms, the launches of 4 to 5 us each being the cost).  Grid: (slices of a geometry's
+// column block, right-hand sides, geometries); a block takes one slice of one pair and leaves the FP64
+// partial of the pair's dot product, and the next kernel's blocks each add the pair's partials in the same
+// fixed order.  The residual norms and flags alternate between two buffers: every block of an iteration
+// reads one, the first block of a pair writes the other.
+constexpr int CG_T = 256;        // threads per block
+constexpr int CG_SLICES = 256;   // most slices of a pair (one partial per thread)
 
 // scalar index of (right-hand side v, geometry g): v * G + g
-__global__ void k_cg_alpha(const double* rr, const double* pap, const int* done, double* alpha, int npair)
+struct CgPair {
+    int64_t pair, off;      // scalar index; first element in the block of vectors
+    int64_t l0, l1;         // the block's slice of the pair's elements
+};
+__device__ __forceinline__ CgPair cg_pair(const int64_t* __restrict__ seg, int64_t n)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= npair) return;
-    alpha[v] = (done[v] || !(pap[v] > 0.0)) ? 0.0 : rr[v] / pap[v];
+    const int v = blockIdx.y, g = blockIdx.z;
+    const int64_t len = seg[2 * g + 1], slice = (len + gridDim.x - 1) / gridDim.x;
+    CgPair c;
+    c.pair = (int64_t)v * gridDim.z + g;
+    c.off = (int64_t)v * n + seg[2 * g];
+    c.l0 = (int64_t)blockIdx.x * slice;
+    c.l1 = min(len, c.l0 + slice);
+    return c;
+}
+// sum over the block, the same for every thread: lanes by halving distances, then the waves in order
+__device__ __forceinline__ double cg_block_sum(double v)
+{
+    __shared__ double red[CG_T / 64];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    __syncthreads();   // the last sum's readers
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = red[0];
+#pragma unroll
+    for (int w = 1; w < CG_T / 64; ++w) t += red[w];
+    return t;
+}
+__device__ __forceinline__ double cg_partials(const double* __restrict__ part, int64_t pair)
+{
+    const int nsl = gridDim.x;
+    return cg_block_sum((int)threadIdx.x < nsl ? part[pair * nsl + threadIdx.x] : 0.0);
 }
 
-// grid (column blocks of the longest geometry, right-hand sides, geometries)
-__global__ void k_cg_xr(float* __restrict__ x, float* __restrict__ r, const float* __restrict__ p,
-                        const float* __restrict__ Ap, const double* __restrict__ alpha,
-                        const int64_t* __restrict__ seg, int64_t n)
+// start: r = p = src (src may be r), x = 0, partials of <r, r>
+__global__ __launch_bounds__(CG_T) void k_cg_start(const float* src, float* r, float* __restrict__ p, float* __restrict__ x,
+                                                   const int64_t* __restrict__ seg, int64_t n, double* __restrict__ part)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y, g = blockIdx.z, G = gridDim.z;
-    if (i >= seg[2 * g + 1]) return;
-    const float a = (float)alpha[(int64_t)v * G + g];
-    if (a != 0.f) {
-        const int64_t o = (int64_t)v * n + seg[2 * g] + i;
-        x[o] += a * p[o];
-        r[o] -= a * Ap[o];
+    const CgPair c = cg_pair(seg, n);
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t i = c.off + c.l0 + threadIdx.x; i < c.off + c.l1; i += CG_T) {
+        const float v = src[i];
+        if (src != r) r[i] = v;
+        p[i] = v;
+        x[i] = 0.f;
+        acc += (double)v * (double)v;
+    }
+    acc = cg_block_sum(acc);
+    if (threadIdx.x == 0) part[c.pair * gridDim.x + blockIdx.x] = acc;
+}
+
+// rr = bb = |A^T y|^2 per pair; a pair with bb = 0 (y orthogonal to the range) is done.  One block per
+// pair, nsl partials each.
+__global__ __launch_bounds__(CG_T) void k_cg_init(const double* __restrict__ part, int nsl, double* rr, double* bb, int* done)
+{
+    const int64_t pair = blockIdx.x;
+    const double s = cg_block_sum((int)threadIdx.x < nsl ? part[pair * nsl + threadIdx.x] : 0.0);
+    if (threadIdx.x == 0) {
+        rr[pair] = bb[pair] = s;
+        done[pair] = s > 0.0 ? 0 : 1;
     }
 }
 
-__global__ void k_cg_beta(double* rr, const double* rr_new, const double* bb, const double* pap, int* done,
-                          double* beta, int npair, double tol2)
+// Ap += lambda p, partials of <p, Ap>
+__global__ __launch_bounds__(CG_T) void k_cg_pap(float* __restrict__ Ap, const float* __restrict__ p, float lam,
+                                                 const int64_t* __restrict__ seg, int64_t n, double* __restrict__ part)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= npair) return;
-    if (done[v]) {
-        beta[v] = 0.0;
-        return;
+    const CgPair c = cg_pair(seg, n);
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t i = c.off + c.l0 + threadIdx.x; i < c.off + c.l1; i += CG_T) {
+        const float pv = p[i];
+        float av = Ap[i];
+        if (lam != 0.f) {
+            av += lam * pv;
+            Ap[i] = av;
+        }
+        acc += (double)pv * (double)av;
     }
-    beta[v] = rr[v] > 0.0 ? rr_new[v] / rr[v] : 0.0;
-    rr[v] = rr_new[v];
-    if (rr_new[v] <= tol2 * bb[v] || !(pap[v] > 0.0)) done[v] = 1;
+    acc = cg_block_sum(acc);
+    if (threadIdx.x == 0) part[c.pair * gridDim.x + blockIdx.x] = acc;
 }
 
-__global__ void k_cg_p(float* __restrict__ p, const float* __restrict__ r, const double* __restrict__ beta,
-                       const int* __restrict__ done, const int64_t* __restrict__ seg, int64_t n)
+// alpha = <r, r> / <p, Ap> (0 for a pair that is done); x += alpha p, r -= alpha Ap, partials of the new <r, r>
+__global__ __launch_bounds__(CG_T) void k_cg_xr(float* __restrict__ x, float* __restrict__ r, const float* __restrict__ p,
+                                                const float* __restrict__ Ap, const double* __restrict__ pap_part,
+                                                const double* __restrict__ rr, const int* __restrict__ done,
+                                                const int64_t* __restrict__ seg, int64_t n, double* __restrict__ pap,
+                                                double* __restrict__ part)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int v = blockIdx.y, g = blockIdx.z, G = gridDim.z;
-    if (i >= seg[2 * g + 1]) return;
-    const int64_t pi = (int64_t)v * G + g;
-    if (!done[pi]) {
-        const int64_t o = (int64_t)v * n + seg[2 * g] + i;
-        p[o] = r[o] + (float)beta[pi] * p[o];
+    const CgPair c = cg_pair(seg, n);
+    const double pa = cg_partials(pap_part, c.pair);
+    const float a = (done[c.pair] || !(pa > 0.0)) ? 0.f : (float)(rr[c.pair] / pa);
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t i = c.off + c.l0 + threadIdx.x; i < c.off + c.l1; i += CG_T) {
+        float rv = r[i];
+        if (a != 0.f) {
+            x[i] += a * p[i];
+            rv -= a * Ap[i];
+            r[i] = rv;
+        }
+        acc += (double)rv * (double)rv;
+    }
+    acc = cg_block_sum(acc);
+    if (threadIdx.x == 0) {
+        part[c.pair * gridDim.x + blockIdx.x] = acc;
+        if (blockIdx.x == 0) pap[c.pair] = pa;
     }
 }
 
-// start: rr = bb = |A^T y|^2 per pair; a pair with bb = 0 (y orthogonal to the range) is done
-__global__ void k_cg_init(double* rr, double* bb, int* done, int npair)
+// beta = new <r, r> / old; the pair is done when the new residual meets the tolerance (or <p, Ap> was not
+// positive), else p = r + beta p.  rr / done: this iteration's, rr_out / done_out: the next one's.
+__global__ __launch_bounds__(CG_T) void k_cg_p(float* __restrict__ p, const float* __restrict__ r,
+                                               const double* __restrict__ rr_part, const double* __restrict__ rr,
+                                               const double* __restrict__ bb, const double* __restrict__ pap,
+                                               const int* __restrict__ done, const int64_t* __restrict__ seg, int64_t n,
+                                               double tol2, double* __restrict__ rr_out, int* __restrict__ done_out)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= npair) return;
-    bb[v] = rr[v];
-    done[v] = rr[v] > 0.0 ? 0 : 1;
+    const CgPair c = cg_pair(seg, n);
+    const double old = rr[c.pair], now = cg_partials(rr_part, c.pair);
+    const int was = done[c.pair];
+    const int is = was || now <= tol2 * bb[c.pair] || !(pap[c.pair] > 0.0);
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        rr_out[c.pair] = was ? old : now;
+        done_out[c.pair] = is;
+    }
+    if (is) return;
+    const float beta = (float)(old > 0.0 ? now / old : 0.0);
+#pragma unroll 4
+    for (int64_t i = c.off + c.l0 + threadIdx.x; i < c.off + c.l1; i += CG_T) p[i] = r[i] + beta * p[i];
 }
 
 __global__ void k_cg_resid(const double* rr, const double* bb, float* out, int npair)
@@ -126,29 +205,23 @@ extern "C" int ridge_solve(const rtt_geometry* g, const float* y, int32_t nrhs, 
     float* p = (float*)ws.get("cg_p", sizeof(float) * (size_t)nrhs * n);
     float* Ap = (float*)ws.get("cg_ap", sizeof(float) * (size_t)nrhs * n);
     float* q = (float*)ws.get("cg_q", sizeof(float) * (size_t)nrhs * m);
-    double* sc = (double*)ws.get("cg_scal", sizeof(double) * 6 * npair);
-    int* done = (int*)ws.get("cg_done", sizeof(int) * npair);
-    if (!r || !p || !Ap || !q || !sc || !done) return fail(RTT_ENOMEM, "ridge_solve workspace");
-    double *rr = sc, *rr_new = sc + npair, *bb = sc + 2 * npair, *pap = sc + 3 * npair, *alpha = sc + 4 * npair,
-           *beta = sc + 5 * npair;
+    const int nsl = (int)std::min<int64_t>(std::max<int64_t>(1, max_cols / 1024), CG_SLICES);
+    double* sc = (double*)ws.get("cg_scal", sizeof(double) * 4 * npair);
+    double* parts = (double*)ws.get("cg_part", sizeof(double) * 2 * (size_t)nsl * npair);
+    int* flags_dev = (int*)ws.get("cg_done", sizeof(int) * 2 * npair);
+    if (!r || !p || !Ap || !q || !sc || !parts || !flags_dev) return fail(RTT_ENOMEM, "ridge_solve workspace");
+    double *rr = sc, *rr_next = sc + npair, *bb = sc + 2 * npair, *pap = sc + 3 * npair;
+    double *pap_part = parts, *rr_part = parts + (size_t)nsl * npair;
+    int *done = flags_dev, *done_next = flags_dev + npair;
     const int64_t* seg = g->d_seg;   // column blocks
     int rc;
-    const dim3 vgrid((unsigned)((n + 255) / 256), (unsigned)nrhs);
-    const dim3 mgrid((unsigned)((max_cols + 255) / 256), (unsigned)nrhs, (unsigned)G);
+    const dim3 grid((unsigned)nsl, (unsigned)nrhs, (unsigned)G), blk(CG_T);
     const dim3 sgrid((unsigned)((npair + 127) / 128));
-    auto pair_dots = [&](const float* a, const float* b, double* out) {
-        return dots_seg(ws, a, n, b, n, seg, G, max_cols, nrhs, out, s);
-    };
     // x = 0, r = A^T y (or the given normal-equation right-hand side), p = r
-    if ((rc = fill(x, (int64_t)nrhs * n, 0.f, s))) return rc;
-    if (normal_rhs) {
-        RTT_HIP(hipMemcpyAsync(r, y, sizeof(float) * (size_t)nrhs * n, hipMemcpyDeviceToDevice, s));
-    } else if ((rc = apply_op(g, -1, true, y, r, nrhs, mask, s))) {
-        return rc;
-    }
-    RTT_HIP(hipMemcpyAsync(p, r, sizeof(float) * (size_t)nrhs * n, hipMemcpyDeviceToDevice, s));
-    if ((rc = pair_dots(r, r, rr))) return rc;
-    hipLaunchKernelGGL(k_cg_init, sgrid, dim3(128), 0, s, rr, bb, done, npair);
+    if (!normal_rhs && (rc = apply_op(g, -1, true, y, r, nrhs, mask, s))) return rc;
+    hipLaunchKernelGGL(k_cg_start, grid, blk, 0, s, normal_rhs ? y : r, r, p, x, seg, n, rr_part);
+    hipLaunchKernelGGL(k_cg_init, dim3((unsigned)npair), blk, 0, s, rr_part, nsl, rr, bb, done);
+    RTT_HIP(hipGetLastError());
     const double tol2 = (double)tol * (double)tol;
     std::vector<double> h_rr(npair), h_bb(npair);
     std::vector<int> h_done(npair);
@@ -165,13 +238,11 @@ extern "C" int ridge_solve(const rtt_geometry* g, const float* y, int32_t nrhs, 
     while (it < maxit) {
         if ((rc = apply_op(g, -1, false, p, q, nrhs, mask, s))) return rc;
         if ((rc = apply_op(g, -1, true, q, Ap, nrhs, mask, s))) return rc;
-        if (lambda != 0.f) hipLaunchKernelGGL(k_axpy_lambda, vgrid, dim3(256), 0, s, Ap, p, n, lambda);
-        if ((rc = pair_dots(p, Ap, pap))) return rc;
-        hipLaunchKernelGGL(k_cg_alpha, sgrid, dim3(128), 0, s, rr, pap, done, alpha, npair);
-        hipLaunchKernelGGL(k_cg_xr, mgrid, dim3(256), 0, s, x, r, p, Ap, alpha, seg, n);
-        if ((rc = pair_dots(r, r, rr_new))) return rc;
-        hipLaunchKernelGGL(k_cg_beta, sgrid, dim3(128), 0, s, rr, rr_new, bb, pap, done, beta, npair, tol2);
-        hipLaunchKernelGGL(k_cg_p, mgrid, dim3(256), 0, s, p, r, beta, done, seg, n);
+        hipLaunchKernelGGL(k_cg_pap, grid, blk, 0, s, Ap, p, lambda, seg, n, pap_part);
+        hipLaunchKernelGGL(k_cg_xr, grid, blk, 0, s, x, r, p, Ap, pap_part, rr, done, seg, n, pap, rr_part);
+        hipLaunchKernelGGL(k_cg_p, grid, blk, 0, s, p, r, rr_part, rr, bb, pap, done, seg, n, tol2, rr_next, done_next);
+        std::swap(rr, rr_next);
+        std::swap(done, done_next);
         RTT_HIP(hipGetLastError());
         ++it;
         if (!async && (it % check_every == 0 || it == maxit)) {

@@ -436,10 +436,10 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_visits, vb);
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_vtask, tb);
     const size_t fb = fwd.size() * sizeof(FwdRec);
+    fwd.resize(fwd.size() + FWD_PAD, FwdRec{});
     const size_t fpad = FWD_PAD * sizeof(FwdRec);
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd, fb + fpad);
-    if (e == hipSuccess) e = hipMemcpy(h->d_fwd, fwd.data(), fb, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset((char*)h->d_fwd + fb, 0, fpad);
+    if (e == hipSuccess) e = hipMemcpy(h->d_fwd, fwd.data(), fb + fpad, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd_row, fb);
     if (e == hipSuccess) e = hipMemcpy(h->d_fwd_row, fwd_row.data(), fb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_rays, recs.data(), rb, hipMemcpyHostToDevice);
