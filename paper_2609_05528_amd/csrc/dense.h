@@ -37,8 +37,17 @@ int gram(Workspace& ws, const float* A, int64_t lda, const float* B, int64_t ldb
 // Out[m][l] = beta*Out[m][l] + sum_k C[k][m] Y[k][l]; C device FP32 K x M row-major.  upper: the
 // caller guarantees C[k][m] = 0 for k > m (e.g. an upper triangular R^-1), and those terms are skipped.
 // run_if as for gram.
-int combine(const float* C, int K, int M, const float* Y, int64_t ldy, float* Out, int64_t ldo, int64_t L,
+int combine(Workspace& ws, const float* C, int K, int M, const float* Y, int64_t ldy, float* Out, int64_t ldo, int64_t L,
             float beta, hipStream_t s, bool upper = false, const int* run_if = nullptr);
+// Products of wide blocks (dense_wide.hip).  gram_split: the upper 32 x 32 tiles of nsplit slice partials of
+// Y Y^T, M = 64, 96 .. 320; gram_split_slices gives the slices.  combine_wide: K >= 16 and
+// (8 ldy + L) * 4 < 2^32; scratch: combine_wide_bytes.
+int gram_split_slices(int64_t L, int64_t* slice);
+void gram_split(const float* Y, int64_t ld, int M, int64_t L, int64_t slice, int nsplit, float* part, hipStream_t s,
+                const int* run_if);
+size_t combine_wide_bytes(int K, int M);
+void combine_wide(void* scratch, const float* C, int K, int M, const float* Y, int64_t ldy, float* Out, int64_t ldo, int64_t L,
+                  float beta, int upper, hipStream_t s, const int* run_if);
 
 // Cholesky QR factors on the device (cholqr.hip), FP64, for ns independent lp x lp Gram matrices
 // stored one after another (lp a multiple of 32, at most 512).  mode 0: first pass (pivots below

@@ -143,7 +143,7 @@ int orth(Ctx& c, float** Y, float** T, int lp, int64_t n, const std::vector<Seg>
         }
         for (int q = 0; q < ns; ++q) {
             const Seg sg = segs[q];
-            if ((rc = combine(Ri32 + q * lp2, lp, lp, *Y + sg.off, n, *T + sg.off, n, sg.len, 0.f, c.s, true,
+            if ((rc = combine(c.ws, Ri32 + q * lp2, lp, lp, *Y + sg.off, n, *T + sg.off, n, sg.len, 0.f, c.s, true,
                               mode == 2 ? st + q : nullptr)))
                 return rc;
         }
@@ -248,11 +248,11 @@ int run_rsvd(Ctx& c, const rtt_svd_opts& o, const float* omega, rtt_svd* res)
         float* Cw = nullptr;
         if ((rc = upload_f32(c, "rs_w", Wk, Wk.size(), &Cw))) return rc;
         const Seg cs = c.cseg[q], rs = c.rseg[q];
-        if ((rc = combine(Cw, l, k, X + cs.off, n, res->V + cs.off, n, cs.len, 0.f, c.s))) return rc;
+        if ((rc = combine(c.ws, Cw, l, k, X + cs.off, n, res->V + cs.off, n, cs.len, 0.f, c.s))) return rc;
         if (o.keep_u) {
             float* Cu = nullptr;
             if ((rc = upload_f32(c, "rs_u", Uk, Uk.size(), &Cu))) return rc;
-            if ((rc = combine(Cu, l, k, Y + rs.off, m, res->U + rs.off, m, rs.len, 0.f, c.s))) return rc;
+            if ((rc = combine(c.ws, Cu, l, k, Y + rs.off, m, res->U + rs.off, m, rs.len, 0.f, c.s))) return rc;
         }
     }
     if (o.keep_u) {
@@ -323,7 +323,7 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
                 for (int mm = 0; mm < b; ++mm) C[(size_t)kk * b + mm] = -Rprev[(size_t)mm * b + kk];
             float* Cf = nullptr;
             if ((rc = upload_f32(c, "lz_c1", C, C.size(), &Cf))) return rc;
-            if ((rc = combine(Cf, b, b, Up, m, W, m, m, 1.f, c.s))) return rc;
+            if ((rc = combine(c.ws, Cf, b, b, Up, m, W, m, m, 1.f, c.s))) return rc;
         }
         if ((rc = orth_r(c, &W, &W2, b, m, rwhole, L))) return rc;   // W now holds U_j
         for (int i = 0; i < b; ++i)
@@ -336,7 +336,7 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
                 for (int mm = 0; mm < b; ++mm) C[(size_t)kk * b + mm] = -L[(size_t)mm * b + kk];
             float* Cf = nullptr;
             if ((rc = upload_f32(c, "lz_c2", C, C.size(), &Cf))) return rc;
-            if ((rc = combine(Cf, b, b, Vj, n, Z, n, n, 1.f, c.s))) return rc;
+            if ((rc = combine(c.ws, Cf, b, b, Vj, n, Z, n, n, 1.f, c.s))) return rc;
         }
         // reorthogonalise twice against all stored right blocks
         const int nv = (j + 1) * b;
@@ -346,7 +346,7 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
             for (auto& v : coef) v = -v;
             float* Cf = nullptr;
             if ((rc = upload_f32(c, "lz_c3", coef, coef.size(), &Cf))) return rc;
-            if ((rc = combine(Cf, nv, b, Vall, n, Z, n, n, 1.f, c.s))) return rc;
+            if ((rc = combine(c.ws, Cf, nv, b, Vall, n, Z, n, n, 1.f, c.s))) return rc;
         }
         if ((rc = orth_r(c, &Z, &Z2, b, n, cwhole, R))) return rc;   // Z = V_{j+1}, R_j
         if (j + 1 < steps) {
@@ -382,7 +382,7 @@ int run_lanczos(Ctx& c, const rtt_svd_opts& o, const float* start, rtt_svd* res)
     float* Cw = nullptr;
     if ((rc = upload_f32(c, "lz_w", Wk, Wk.size(), &Cw))) return rc;
     if (!(res->V = (float*)res->take(sizeof(float) * (size_t)k * n))) return fail(RTT_ENOMEM, "right factors");
-    if ((rc = combine(Cw, mdim, k, Vall, n, res->V, n, n, 0.f, c.s))) return rc;
+    if ((rc = combine(c.ws, Cw, mdim, k, Vall, n, res->V, n, n, 0.f, c.s))) return rc;
     RTT_HIP(hipStreamSynchronize(c.s));
     return RTT_OK;
 }
@@ -531,7 +531,7 @@ static int tsvd_apply(const rtt_geometry* g, const rtt_svd* sv, const float* y, 
     for (int q = 0; q < sets; ++q) {
         const int64_t off = sets > 1 ? g->members[q].col_offset : 0;
         const int64_t len = sets > 1 ? g->members[q].n_cols : n;
-        if ((rc = combine(Cf + (size_t)q * tt * nrhs, tt, nrhs, sv->V + off, n, x + off, n, len, 0.f, s))) return rc;
+        if ((rc = combine(ws, Cf + (size_t)q * tt * nrhs, tt, nrhs, sv->V + off, n, x + off, n, len, 0.f, s))) return rc;
     }
     return RTT_OK;
 }

@@ -419,7 +419,7 @@ extern "C" int synth_expand(const rtt_synthesis* s, const float* c, float* x, in
     const int64_t tot = (int64_t)s->d * nvec;
     hipLaunchKernelGGL(k_transpose_f32, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, c, nvec, s->d, Ct);
     RTT_HIP(hipGetLastError());
-    return combine(Ct, s->d, nvec, s->d_Q, s->n_cols, x, s->n_cols, s->n_cols, 0.f, st);
+    return combine(s->ws, Ct, s->d, nvec, s->d_Q, s->n_cols, x, s->n_cols, s->n_cols, 0.f, st);
 }
 
 extern "C" int synth_project(const rtt_synthesis* s, const float* x, float* c, int32_t nvec, void* stream)

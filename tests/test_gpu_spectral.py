@@ -362,3 +362,22 @@ def test_block_lanczos_512_vectors_on_the_large_geometry(gpu_lib):
     v2 = sv.V()[1].double().cpu().numpy()
     v2 /= np.linalg.norm(v2)
     assert abs(np.linalg.norm(oracle.forward(geo, v2)) - th[1]) <= 1e-4 * th[0]
+
+
+@pytest.mark.parametrize("k,p", [(33, 8), (64, 1), (90, 6), (150, 10), (310, 10), (330, 2)])
+def test_rsvd_at_the_edges_of_the_split_products(gpu_lib, k, p):
+    """Sketches of 64, 96, 160 and 320 padded vectors (one tile list per width), one past the widest
+    split Gram (352), and k = 33 .. 64 (the last 16-row step of the combine moves back): sigma against the
+    oracle's rSVD on the same test block (1e-4 on sigma >= 1e-3 sigma_1) and V V^T = I to 2e-5 (products of at
+    most 352 FP32 terms)."""
+    rtt = gpu_lib
+    geo = tiny_geometry(seed=240, rays=(61, 11, 9), n_r=5, n_phi=7, n_frames=17)
+    G = rtt.Geometry(geo)
+    say("case rsvd split", k, p, G.n_rows, G.n_cols)
+    om = np.random.default_rng(11).standard_normal((k + p, G.n_cols)).astype(np.float32)
+    s_o, _, _ = oracle.rsvd(geo, om.astype(np.float64), q=1)
+    sv = rtt.rsvd(G, k=k, p=p, q=1, omega=to_dev(om))
+    ok = s_o[:k] >= 1e-3 * s_o[0]
+    assert np.max(np.abs(sv.sigma[ok] - s_o[:k][ok]) / s_o[:k][ok]) <= 1e-4
+    V = sv.V().double().cpu().numpy()[ok]
+    assert np.max(np.abs(V @ V.T - np.eye(V.shape[0]))) <= 2e-5
