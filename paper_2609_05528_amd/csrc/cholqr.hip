@@ -3,17 +3,18 @@
 // the singular values of Sec. 3.6 eq. (19) and Sec. 4.4 eq. (31)).  For ns independent
 // problems at once, each an lp x lp Gram matrix G = Y Y^T (lp a multiple of 32, at most 512):
 //
-//   k_chol_factor   G = R^T R (R upper), one workgroup per problem: panels of 32 rows, each
-//                   factored by all threads (one column per thread, in registers), the rows below
-//                   it then updated from the panel kept in LDS.
-//                   Every entry receives its terms in increasing row order (the order of the
-//                   textbook column formula), product and difference rounded separately.  Pivots
+//   k_chol_step     G = R^T R (R upper) and R^-1, one launch per row of 32 x 32 blocks and one more: a
+//                   workgroup per block of the row sums its terms left-looking, and one wave factors
+//                   the diagonal block (every workgroup its own copy) together with the block's columns;
+//                   the other workgroups form the previous block column of R^-1.
+//   k_chol_factor / k_chol_diag_inv / k_chol_offdiag_inv
+//                   the same on one workgroup per problem, in one launch each: the passes that run only
+//                   where a flag is set on the device.  Pivots
 //                   at or below dead_tol * max diag(G) mark dependent columns: zero diagonal and
 //                   row, their projection coefficients R[k][j] (k < j) kept.  On a first pass a pivot below
 //                   1e-5 max diag(G) (past the FP32 accuracy of the Gram matrix) re-factors
 //                   G + 1e-6 max diag(G) I and flags one more pass (shifted CholQR3, Fukaya et
 //                   al. 2020); the extra pass runs only where that flag is set.
-//   k_chol_diag_inv / k_chol_offdiag_inv
 //                   R^-1 on the independent columns (dependent rows and columns zero), blocked:
 //                   the 32 x 32 diagonal blocks by back substitution, then block column J from
 //                   X_IJ = -R_II^-1 sum_{K=I+1..J} R_IK X_KJ for I = J-1 .. 0; written in FP64 and
@@ -67,16 +68,246 @@ __device__ double block_reduce(double v, int op, double* red)
     return r;
 }
 
-// mode 0: first pass (may shift, sets st[q]); 1: plain pass; 2: the conditional pass (only where
-// st[q] != 0).  S: scratch lp x lp per problem.  R: lp x lp per problem, written in full (zero
+// The row p of blocks of R, and the block column p - 1 of R^-1 (p = 0 .. T, T = lp / 32 blocks).  Grid (T,
+// problems): workgroup x < T - p makes block J = p + x of the row, the others block I = x - (T - p) of the
+// column.  One workgroup had factored a 288 x 288 matrix in 0.46 ms and inverted it in 0.13, bound by its
+// barriers, by the square root and division of each of 288 dependent steps, and by one CU's updates; the ten
+// launches take 0.20 ms (rank-256 rSVD 26.5 -> 23.5 ms).  The pivot's reciprocal root comes from the hardware estimate and three Newton steps, and
+// rows reach the other lanes as scalars (readlane), so a step has no LDS round trip and no barrier.
+__global__ __launch_bounds__(512) void k_chol_step(const double* __restrict__ G, double* __restrict__ R, double* __restrict__ Ri,
+                                                   float* __restrict__ Ri32, int* __restrict__ dead, int lp, int p,
+                                                   double dead_tol)
+{
+    const int q = blockIdx.y, T = lp / CB;
+    const size_t lp2 = (size_t)lp * lp;
+    G += q * lp2;
+    R += q * lp2;
+    Ri += q * lp2;
+    Ri32 += q * lp2;
+    dead += (size_t)q * lp;
+    __shared__ double tile[2][2][CB][CB + 2];   // per k group: two 32 x 32 operands
+    __shared__ double W[CB][2 * CB + 2];
+    __shared__ double red[16];
+    const int t = threadIdx.x, lane = t & 63;
+    const int grp = t >> 8, u = t & 255;        // two groups of 256 threads share the blocks of a sum
+    const int a = (u >> 4) * 2, b = (u & 15) * 2;   // this thread's 2 x 2 entries of a block
+    const bool first = (int)blockIdx.x < T - p;
+
+    // acc = sum over blocks K = k0 .. k1 - 1 of op1(K)^T or op1(K) times op2(K); tiles hold [k][column]
+    auto sum_blocks = [&](int k0, int k1, const double* m1, size_t row1, size_t col1, bool t1, const double* m2, size_t col2,
+                          double (&acc)[2][2], double (&acc2)[2][2], bool twice) {
+        double n1[4], n2[4];
+        // op1 block K: rows 32 K .. of column block col1 (t1: the rows are the summed index), or rows row1 of
+        // column block 32 K; op2 block K: rows 32 K .. of column block col2
+        auto fetch = [&](int K) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = u + 256 * i, r = e >> 5, c = e & 31;
+                n1[i] = t1 ? m1[(size_t)(K * CB + r) * lp + col1 + c] : m1[(row1 + r) * lp + (size_t)K * CB + c];
+                n2[i] = m2[(size_t)(K * CB + r) * lp + col2 + c];
+            }
+        };
+        const int n = k1 - k0, steps = (n + 1) / 2;
+        if (grp < n) fetch(k0 + grp);
+        for (int s = 0; s < steps; ++s) {
+            const int K = k0 + 2 * s + grp;
+            const bool have = K < k1;
+            __syncthreads();
+            if (have) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int e = u + 256 * i, r = e >> 5, c = e & 31;
+                    if (t1) tile[grp][0][r][c] = n1[i];
+                    else tile[grp][0][c][r] = n1[i];
+                    tile[grp][1][r][c] = n2[i];
+                }
+                if (K + 2 < k1) fetch(K + 2);
+            }
+            __syncthreads();
+            if (have) {
+#pragma unroll 4
+                for (int k = 0; k < CB; ++k) {
+                    const double x0 = tile[grp][0][k][a], x1 = tile[grp][0][k][a + 1];
+                    const double y0 = tile[grp][1][k][b], y1 = tile[grp][1][k][b + 1];
+                    acc[0][0] += x0 * y0;
+                    acc[0][1] += x0 * y1;
+                    acc[1][0] += x1 * y0;
+                    acc[1][1] += x1 * y1;
+                    if (twice) {
+                        const double z0 = tile[grp][0][k][b], z1 = tile[grp][0][k][b + 1];
+                        acc2[0][0] += x0 * z0;
+                        acc2[0][1] += x0 * z1;
+                        acc2[1][0] += x1 * z0;
+                        acc2[1][1] += x1 * z1;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    };
+
+    if (first) {
+        const int J = p + (int)blockIdx.x, p0 = p * CB, j0 = J * CB;
+        double md = 0.0;
+        for (int j = t; j < lp; j += 512) md = fmax(md, G[(size_t)j * lp + j]);
+        const double maxdiag = uniform_f64(block_reduce(md, 0, red));
+        const double tol = dead_tol * maxdiag;
+        const bool all_dead = !(maxdiag > 0.0);
+        double B[2][2] = {{0.0, 0.0}, {0.0, 0.0}}, D[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        sum_blocks(0, p, R, 0, p0, true, R, j0, B, D, true);
+        // W = G - sums: columns 0 .. 31 the diagonal block, 32 .. 63 block J
+        if (grp == 1)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    W[a + i][b + k] = D[i][k];
+                    W[a + i][CB + b + k] = B[i][k];
+                }
+        __syncthreads();
+        if (grp == 0)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const size_t row = (size_t)(p0 + a + i) * lp;
+                    W[a + i][b + k] = G[row + p0 + b + k] - (D[i][k] + W[a + i][b + k]);
+                    W[a + i][CB + b + k] = G[row + j0 + b + k] - (B[i][k] + W[a + i][CB + b + k]);
+                }
+        __syncthreads();
+        if (J == p)   // zeros left of the diagonal block
+            for (int e = t; e < CB * p0; e += 512) R[(size_t)(p0 + e / p0) * lp + e % p0] = 0.0;
+        if (t >= 64) return;
+        double s[CB];
+#pragma unroll
+        for (int i = 0; i < CB; ++i) s[i] = W[i][lane];
+        auto from_lane = [](double v, int l) {
+            const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
+            const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)bits, l);
+            const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(bits >> 32), l);
+            return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+        };
+        unsigned dead_bits = 0;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+            const double d = from_lane(s[j], j);
+            const bool dj = !(d > tol) || all_dead;
+            const double dd = dj ? 1.0 : d;
+            double y = __builtin_amdgcn_rsq(dd);
+#pragma unroll
+            for (int n = 0; n < 3; ++n) y = fma(y * 0.5, fma(-dd * y, y, 1.0), y);
+            const double rjj = dd * y;
+            const double r = dj ? 0.0 : (lane == j ? rjj : (lane > j ? s[j] * y : 0.0));
+            dead_bits |= dj ? 1u << j : 0u;
+            s[j] = r;
+#pragma unroll
+            for (int i = j + 1; i < CB; ++i) s[i] = fma(-from_lane(r, i), r, s[i]);
+        }
+        const bool mine = lane < CB ? J == p : J != p;
+        const size_t col = lane < CB ? p0 + lane : j0 + lane - CB;
+        if (mine)
+#pragma unroll
+            for (int i = 0; i < CB; ++i) R[(size_t)(p0 + i) * lp + col] = s[i];
+        if (J == p && lane < CB) dead[p0 + lane] = (int)(dead_bits >> lane) & 1;
+        return;
+    }
+
+    // R^-1: X_II = R_II^-1, X_IP = -(sum_{K = I .. P - 1} X_IK R_KP) X_PP with P = p - 1
+    const int I = (int)blockIdx.x - (T - p), P = p - 1, i0 = I * CB, P0 = P * CB;
+    for (int e = t; e < CB * CB; e += 512) W[e >> 5][e & 31] = R[(size_t)(P0 + (e >> 5)) * lp + P0 + (e & 31)];
+    __syncthreads();
+    if (t < CB) {   // column t of X_PP, right-looking back substitution; dependent rows and columns are zero
+        const bool dc = dead[P0 + t] != 0;
+        unsigned db = 0;
+        for (int k = 0; k < CB; ++k) db |= dead[P0 + k] != 0 ? 1u << k : 0u;
+        const double rinv = ((db >> t) & 1u) ? 0.0 : 1.0 / W[t][t];
+        W[t][CB] = rinv;
+        double x[CB];
+#pragma unroll
+        for (int i = 0; i < CB; ++i) x[i] = (i == t && !dc) ? 1.0 : 0.0;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int k = CB - 1; k >= 0; --k) {
+            x[k] *= W[k][CB];
+#pragma unroll
+            for (int i = 0; i < k; ++i) x[i] = fma(-W[i][k], x[k], x[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < CB; ++i) W[i][CB + 1 + t] = x[i];
+    }
+    __syncthreads();
+    if (I == P) {
+        for (int e = t; e < CB * CB; e += 512) {
+            const double v = W[e >> 5][CB + 1 + (e & 31)];
+            const size_t o = (size_t)(P0 + (e >> 5)) * lp + P0 + (e & 31);
+            Ri[o] = v;
+            Ri32[o] = (float)v;
+        }
+        for (int e = t; e < CB * (lp - P0 - CB); e += 512) {   // zeros below the diagonal block
+            const size_t o = (size_t)(P0 + CB + (e >> 5)) * lp + P0 + (e & 31);
+            Ri[o] = 0.0;
+            Ri32[o] = 0.f;
+        }
+        return;
+    }
+    double S2[2][2] = {{0.0, 0.0}, {0.0, 0.0}}, unused[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+    sum_blocks(I, P, Ri, i0, 0, false, R, P0, S2, unused, false);
+    // the groups' sums added in tile[0][0], then times X_PP
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (grp == 1) tile[0][0][a + i][b + k] = S2[i][k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (grp == 0) tile[0][0][a + i][b + k] += S2[i][k];
+    __syncthreads();
+    for (int e = t; e < CB * CB; e += 512) {
+        const int r = e >> 5, c = e & 31;
+        double v = 0.0;
+#pragma unroll 8
+        for (int k = 0; k < CB; ++k) v += tile[0][0][r][k] * W[k][CB + 1 + c];
+        const size_t o = (size_t)(i0 + r) * lp + P0 + c;
+        Ri[o] = -v;
+        Ri32[o] = (float)-v;
+    }
+}
+
+// After a first pass: st[q] = 1 where the smallest independent pivot is past the FP32 accuracy of the Gram
+// matrix (below 1e-5 max diag), else 0.
+__global__ __launch_bounds__(512) void k_chol_check(const double* __restrict__ G, const double* __restrict__ R,
+                                                    const int* __restrict__ dead, int* __restrict__ st, int lp)
+{
+    __shared__ double red[16];
+    const int q = blockIdx.x, t = threadIdx.x;
+    const size_t lp2 = (size_t)lp * lp;
+    double md = 0.0, mp = INFINITY;
+    for (int j = t; j < lp; j += 512) {
+        md = fmax(md, G[q * lp2 + (size_t)j * lp + j]);
+        if (!dead[(size_t)q * lp + j]) {
+            const double r = R[q * lp2 + (size_t)j * lp + j];
+            mp = fmin(mp, r * r);
+        }
+    }
+    const double maxdiag = block_reduce(md, 0, red), minpiv = block_reduce(mp, 1, red);
+    if (t == 0) st[q] = minpiv < 1e-5 * maxdiag ? 1 : 0;
+}
+
+// One workgroup per problem, only where st[q] != 0: shift != 0 factors G + shift max diag(G) I (the second
+// attempt of a first pass), shift = 0 is the conditional pass.  S: scratch lp x lp per problem.  R: lp x lp per problem, written in full (zero
 // below the diagonal).  dead: lp flags per problem.  512 threads.
 __global__ __launch_bounds__(512) void k_chol_factor(const double* __restrict__ G, double* __restrict__ S,
                                                      double* __restrict__ R, int* __restrict__ dead,
-                                                     int* __restrict__ st, int lp, int mode, double dead_tol)
+                                                     const int* __restrict__ st, int lp, double rel_shift, double dead_tol)
 {
 #pragma clang fp contract(off)
     const int q = blockIdx.x;
-    if (mode == 2 && st[q] == 0) return;
+    if (st[q] == 0) return;
     const size_t lp2 = (size_t)lp * lp;
     G += q * lp2;
     S += q * lp2;
@@ -93,8 +324,8 @@ __global__ __launch_bounds__(512) void k_chol_factor(const double* __restrict__ 
     const double tol = dead_tol * maxdiag;
     const bool all_dead = !(maxdiag > 0.0);
 
-    double shift = 0.0;
-    for (int attempt = 0; attempt < 2; ++attempt) {
+    const double shift = rel_shift * maxdiag;
+    {
         // flat over the entries, unrolled so that a thread has eight loads of G in flight (one
         // load-store round trip per entry had left this copy latency-bound)
         const int n2 = lp * lp;
@@ -191,31 +422,17 @@ __global__ __launch_bounds__(512) void k_chol_factor(const double* __restrict__ 
             }
             __syncthreads();
         }
-        if (mode != 0 || attempt == 1) break;
-        // first pass: the smallest independent pivot against the FP32 accuracy of the Gram matrix
-        double mp = INFINITY;
-        for (int j = t; j < lp; j += blockDim.x)
-            if (!dead[j]) {
-                const double r = R[(size_t)j * lp + j];
-                mp = fmin(mp, r * r);
-            }
-        const double minpiv = block_reduce(mp, 1, red);
-        const bool shifted = minpiv < 1e-5 * maxdiag;
-        if (t == 0) st[q] = shifted ? 1 : 0;
-        if (!shifted) break;
-        shift = 1e-6 * maxdiag;
-        __syncthreads();
     }
 }
 
 // The inverses of the 32 x 32 diagonal blocks of R (one wave per block; lane c solves column c
 // by back substitution, sums in increasing k).  Ri and Ri32: lp x lp per problem.
 __global__ __launch_bounds__(64) void k_chol_diag_inv(const double* __restrict__ R, const int* __restrict__ dead,
-                                                      const int* __restrict__ st, int lp, int mode,
-                                                      double* __restrict__ Ri, float* __restrict__ Ri32)
+                                                      const int* __restrict__ st, int lp, double* __restrict__ Ri,
+                                                      float* __restrict__ Ri32)
 {
     const int q = blockIdx.y, b0 = blockIdx.x * CB;
-    if (mode == 2 && st[q] == 0) return;
+    if (st[q] == 0) return;
     const size_t lp2 = (size_t)lp * lp;
     R += q * lp2;
     Ri += q * lp2;
@@ -255,11 +472,10 @@ __global__ __launch_bounds__(64) void k_chol_diag_inv(const double* __restrict__
 // step I every thread first loads its element of each 32 x 32 block R_IK (K = I+1 .. J) into
 // registers -- one round trip for all of them -- and the blocks then pass through LDS one by one.
 __global__ __launch_bounds__(1024) void k_chol_offdiag_inv(const double* __restrict__ R, const int* __restrict__ st,
-                                                           int lp, int mode, double* __restrict__ Ri,
-                                                           float* __restrict__ Ri32)
+                                                           int lp, double* __restrict__ Ri, float* __restrict__ Ri32)
 {
     const int q = blockIdx.y, J = blockIdx.x;
-    if (mode == 2 && st[q] == 0) return;
+    if (st[q] == 0) return;
     const size_t lp2 = (size_t)lp * lp;
     R += q * lp2;
     Ri += q * lp2;
@@ -369,23 +585,25 @@ __global__ void k_copy_rows_if(const int* __restrict__ run_if, const float* __re
 }  // namespace
 
 int chol_factor(const double* G, int lp, int ns, int mode, double dead_tol, double* S, double* R, int* dead, int* st,
-                hipStream_t s)
+                double* Ri, float* Ri32, hipStream_t s)
 {
     if (lp % CB || lp <= 0 || lp > CQ_MAX || ns <= 0) return fail(RTT_EINVAL, "chol_factor: bad size");
-    // 512 threads: one per column right of a panel (at most 480), 256 registers each for the
-    // panel column held in registers
-    hipLaunchKernelGGL(k_chol_factor, dim3((unsigned)ns), dim3(512), 0, s, G, S, R, dead, st, lp, mode, dead_tol);
-    RTT_HIP(hipGetLastError());
-    return RTT_OK;
-}
-
-int chol_inverse(const double* R, const int* dead, const int* st, int lp, int ns, int mode, double* Ri, float* Ri32,
-                 hipStream_t s)
-{
-    if (lp % CB || lp <= 0 || lp > CQ_MAX || ns <= 0) return fail(RTT_EINVAL, "chol_inverse: bad size");
-    const dim3 grid((unsigned)(lp / CB), (unsigned)ns);
-    hipLaunchKernelGGL(k_chol_diag_inv, grid, dim3(64), 0, s, R, dead, st, lp, mode, Ri, Ri32);
-    hipLaunchKernelGGL(k_chol_offdiag_inv, grid, dim3(1024), 0, s, R, st, lp, mode, Ri, Ri32);
+    const int T = lp / CB;
+    if (mode != 2) {
+        for (int p = 0; p <= T; ++p)
+            hipLaunchKernelGGL(k_chol_step, dim3((unsigned)T, (unsigned)ns), dim3(512), 0, s, G, R, Ri, Ri32, dead, lp, p, dead_tol);
+        if (mode == 0)
+            hipLaunchKernelGGL(k_chol_check, dim3((unsigned)ns), dim3(512), 0, s, G, R, dead, st, lp);
+    }
+    if (mode != 1) {
+        // where st[q] != 0: the shifted second attempt of a first pass, or the conditional pass.  512 threads:
+        // one per column right of a panel (at most 480), 256 registers each for the panel column
+        hipLaunchKernelGGL(k_chol_factor, dim3((unsigned)ns), dim3(512), 0, s, G, S, R, dead, st, lp, mode == 0 ? 1e-6 : 0.0,
+                           dead_tol);
+        const dim3 grid((unsigned)T, (unsigned)ns);
+        hipLaunchKernelGGL(k_chol_diag_inv, grid, dim3(64), 0, s, R, dead, st, lp, Ri, Ri32);
+        hipLaunchKernelGGL(k_chol_offdiag_inv, grid, dim3(1024), 0, s, R, st, lp, Ri, Ri32);
+    }
     RTT_HIP(hipGetLastError());
     return RTT_OK;
 }

@@ -55,11 +55,9 @@ void combine_wide(void* scratch, const float* C, int K, int M, const float* Y, i
 // further pass; mode 2: the conditional pass, only for problems with st[q] != 0 (the others are
 // left untouched).  dead_tol: pivots at or below dead_tol * max diag mark dependent columns
 // (dead[q*lp + j] = 1; zero diagonal and row).  S is lp x lp scratch per problem.
-int chol_factor(const double* G, int lp, int ns, int mode, double dead_tol, double* S, double* R, int* dead, int* st,
-                hipStream_t s);
 // Ri = R^-1 on the independent columns (dependent rows and columns zero), FP64 and FP32 copies.
-int chol_inverse(const double* R, const int* dead, const int* st, int lp, int ns, int mode, double* Ri, float* Ri32,
-                 hipStream_t s);
+int chol_factor(const double* G, int lp, int ns, int mode, double dead_tol, double* S, double* R, int* dead, int* st,
+                double* Ri, float* Ri32, hipStream_t s);
 // C = A B for upper triangular A, B; in mode 2, C = B for problems with st[q] == 0.
 int upper_product(const double* A, const double* B, const int* st, int lp, int ns, int mode, double* C, hipStream_t s);
 // ns identity matrices lp x lp.

@@ -135,8 +135,7 @@ int orth(Ctx& c, float** Y, float** T, int lp, int64_t n, const std::vector<Seg>
                            mode == 2 ? st + q : nullptr)))
                 return rc;
         }
-        if ((rc = chol_factor(Gd, lp, ns, mode, dead_tol, S, R, dead, st, c.s))) return rc;
-        if ((rc = chol_inverse(R, dead, st, lp, ns, mode, Ri, Ri32, c.s))) return rc;
+        if ((rc = chol_factor(Gd, lp, ns, mode, dead_tol, S, R, dead, st, Ri, Ri32, c.s))) return rc;
         if (R_out) {
             if ((rc = upper_product(R, rt[cur], st, lp, ns, mode, rt[1 - cur], c.s))) return rc;
             cur = 1 - cur;
