@@ -563,6 +563,13 @@ __global__ __launch_bounds__(1024) void k_upper_product(const double* __restrict
     C[(size_t)i * lp + j] = v;
 }
 
+__global__ void k_neg_coef(const double* __restrict__ A, int rows, int cols, int transpose, float* __restrict__ C)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= rows * cols) return;
+    C[e] = (float)-A[transpose ? (e % cols) * rows + e / cols : e];
+}
+
 __global__ void k_identity_f64(double* __restrict__ R, int lp, int64_t n)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -613,6 +620,15 @@ int upper_product(const double* A, const double* B, const int* st, int lp, int n
     if (lp % CB || lp <= 0 || lp > CQ_MAX || ns <= 0) return fail(RTT_EINVAL, "upper_product: bad size");
     hipLaunchKernelGGL(k_upper_product, dim3((unsigned)(lp / CB), (unsigned)(lp / CB), (unsigned)ns), dim3(1024), 0, s,
                        A, B, st, lp, mode, C);
+    RTT_HIP(hipGetLastError());
+    return RTT_OK;
+}
+
+int neg_coef(const double* A, int rows, int cols, bool transpose, float* C, hipStream_t s)
+{
+    const int n = rows * cols;
+    if (n <= 0) return RTT_OK;
+    hipLaunchKernelGGL(k_neg_coef, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A, rows, cols, transpose ? 1 : 0, C);
     RTT_HIP(hipGetLastError());
     return RTT_OK;
 }

@@ -60,6 +60,9 @@ int chol_factor(const double* G, int lp, int ns, int mode, double dead_tol, doub
                 double* Ri, float* Ri32, hipStream_t s);
 // C = A B for upper triangular A, B; in mode 2, C = B for problems with st[q] == 0.
 int upper_product(const double* A, const double* B, const int* st, int lp, int ns, int mode, double* C, hipStream_t s);
+// C = -A in FP32 for A (rows x cols, FP64), or C[k][m] = -A[m][k] (rows = cols) when transpose: the coefficient
+// blocks of the block Lanczos recurrences.
+int neg_coef(const double* A, int rows, int cols, bool transpose, float* C, hipStream_t s);
 // ns identity matrices lp x lp.
 int identity_f64(double* R, int lp, int ns, hipStream_t s);
 // dst = src over rows x len (row stride ld) when *run_if != 0.
