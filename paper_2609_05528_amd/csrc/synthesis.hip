@@ -31,6 +31,9 @@ struct rtt_synthesis {
     float* d_Q = nullptr;     // [d][n_cols]: row (a, b, c) = column (a, b, c) of Q
     // FP32 factor tables of the separable path: R [n_radial][n_r], P [n_az][n_phi], T [n_temporal][K]
     float *d_R = nullptr, *d_P = nullptr, *d_T = nullptr;
+    // P by cells for the wave kernels: [n_phi + 8][nb], zero past n_az functions and n_phi cells
+    float* d_Pt = nullptr;
+    int32_t nb = 0;
     int32_t n_r = 0, n_phi = 0, K = 0;
     bool separable = false;   // the factor-by-factor kernels fit their LDS limits
     int device = 0;
@@ -197,6 +200,152 @@ __global__ void k_synth_project_sum(const float* __restrict__ part, int n_r, int
     c[t] = (float)acc;
 }
 
+// One wave per (radial node i, vector v, 64 hats): lane l holds hat k = 64 blockIdx.z + l mod LK of the cells
+// j = row group l / LK, LK the power of two above the hats of the chunk.  UNI: one row group, so that the
+// azimuth factors of a cell are scalar loads.  NB >= n_az azimuth functions stay in registers.
+//
+// c -> x: V[b][k] = sum_c T[c][k] (sum_a R[a][i] c[a][b][c]), then x[i][j][k] = sum_b P[b][j] V[b][k]
+// (one pass of stores).  Bound by the stores: 264 vectors of 64 x 96 x 64 nodes 91 us (block kernel 288),
+// 415 MB at 4.6 TB/s (a fill of it takes 60).
+template <int NB, bool UNI>
+__global__ __launch_bounds__(256) void k_synth_expand_wave(const float* __restrict__ R, const float* __restrict__ Pt,
+                                                           const float* __restrict__ T, int nR, int nA, int nT,
+                                                           int n_r, int n_phi, int K, int lk_log,
+                                                           const float* __restrict__ c, float* __restrict__ x,
+                                                           int64_t n_cols)
+{
+    extern __shared__ float lds[];    // nA * nT: the coefficients with the radial factor of node i applied
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
+    const int i = blockIdx.x;
+    const int64_t v = blockIdx.y;
+    const int kl = UNI ? lane : lane & ((1 << lk_log) - 1), rg = UNI ? 0 : lane >> lk_log;
+    const int k = blockIdx.z * 64 + kl, kc = min(k, K - 1);
+    const int RG = UNI ? 1 : 64 >> lk_log;
+    const int bq = nA * nT;
+    for (int o = threadIdx.x; o < bq; o += blockDim.x) {
+        float acc = 0.f;
+        for (int a = 0; a < nR; ++a) acc += R[a * n_r + i] * c[v * nR * bq + a * bq + o];
+        lds[o] = acc;
+    }
+    __syncthreads();
+    float V[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) V[b] = 0.f;
+    for (int q = 0; q < nT; ++q) {
+        const float t = T[q * K + kc];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            if (b < nA) V[b] += t * lds[b * nT + q];
+    }
+    const int per = (n_phi + nw - 1) / nw, j1 = min(n_phi, wave * per + per);
+    float* __restrict__ xr = x + v * n_cols + (int64_t)i * n_phi * K;
+    if (k >= K) return;
+#pragma unroll 4
+    for (int j = wave * per + rg; j < j1; j += RG) {
+        float acc = 0.f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc += Pt[j * NB + b] * V[b];
+        xr[j * K + k] = acc;
+    }
+}
+
+// x -> c: U[b][k] = sum_j P[b][j] x[i][j][k] on the way through x (read once, straight to registers), then
+// Z[v][i][chunk][b][c] = sum_k T[c][k] U[b][k] from LDS; k_synth_radial_sum applies the radial factors.  Bound by
+// the read of x: 264 vectors of 64 x 96 x 64 nodes 137 us (block kernel 512), 415 MB at 3.0 TB/s.  The block kernel
+// contracted the hats first: every thread walked a row of x in LDS, 8 times the operations.
+template <int NB, bool UNI>
+__global__ __launch_bounds__(256) void k_synth_project_wave(const float* __restrict__ Pt, const float* __restrict__ T,
+                                                            int nA, int nT, int n_r, int n_phi, int K, int lk_log,
+                                                            const float* __restrict__ x, int64_t n_cols,
+                                                            float* __restrict__ Z)
+{
+    constexpr int LD = 68;            // row stride of U: rows a bank group apart, 16-byte aligned
+    constexpr int UNROLL = 8;
+    extern __shared__ __attribute__((aligned(16))) float us[];   // [waves][NB][LD]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
+    const int i = blockIdx.x;
+    const int64_t v = blockIdx.y;
+    const int kl = UNI ? lane : lane & ((1 << lk_log) - 1), rg = UNI ? 0 : lane >> lk_log;
+    const int k0 = blockIdx.z * 64, k = k0 + kl;
+    const int RG = UNI ? 1 : 64 >> lk_log;
+    const int per = (n_phi + nw - 1) / nw, j1 = min(n_phi, wave * per + per);
+    const float* __restrict__ xr = x + v * n_cols + (int64_t)i * n_phi * K;
+    float acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = 0.f;
+    // lanes past the last hat read it again: their sums are not used
+    const float* __restrict__ xk = xr + min(k, K - 1);
+    const int j0 = wave * per;
+    int jb = j0;
+    for (; jb + UNROLL * RG <= j1; jb += UNROLL * RG) {
+        float xv[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) xv[u] = xk[(jb + u * RG + rg) * K];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] += Pt[(jb + u * RG + rg) * NB + b] * xv[u];
+    }
+    for (int j = jb + rg; j < j1; j += RG) {
+        const float xv = xk[j * K];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] += Pt[j * NB + b] * xv;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) us[(wave * NB + b) * LD + lane] = acc[b];
+    __syncthreads();
+    if (nw > 1) {
+        for (int e = threadIdx.x; e < NB * 64; e += blockDim.x) {
+            const int at = (e >> 6) * LD + (e & 63);
+            float t = us[at];
+            for (int w = 1; w < nw; ++w) t += us[w * NB * LD + at];
+            us[at] = t;
+        }
+        __syncthreads();
+    }
+    const int bq = nA * nT, nk = min(64, K - k0);
+    float* __restrict__ zr = Z + ((v * n_r + i) * gridDim.z + blockIdx.z) * bq;
+    for (int o = threadIdx.x; o < bq; o += blockDim.x) {
+        const float* __restrict__ t = T + (o % nT) * K + k0;
+        const float* u = us + (o / nT) * LD;
+        float z[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < RG; ++g) {
+            int q = 0;
+#pragma unroll 4
+            for (; q + 4 <= nk; q += 4)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] += t[q + r] * u[(UNI ? 0 : g << lk_log) + q + r];
+            for (; q < nk; ++q) z[0] += t[q] * u[(UNI ? 0 : g << lk_log) + q];
+        }
+        zr[o] = (z[0] + z[1]) + (z[2] + z[3]);
+    }
+}
+
+// c[v][a][o] = sum over radial nodes i and hat chunks of R[a][i] Z[v][i][chunk][o], in FP64: 64 outputs a
+// block, four threads an output over every fourth (node, chunk), added in a fixed order
+__global__ __launch_bounds__(256) void k_synth_radial_sum(const float* __restrict__ R, const float* __restrict__ Z,
+                                                          int nR, int bq, int n_r, int chunks, int64_t tot,
+                                                          float* __restrict__ c)
+{
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * 64 + lane, tc = min(t, tot - 1);
+    const int d = nR * bq;
+    const int64_t v = tc / d;
+    const int q = (int)(tc % d), a = q / bq, o = q % bq;
+    const float* __restrict__ z = Z + v * n_r * chunks * bq + o;
+    const float* __restrict__ r = R + (int64_t)a * n_r;
+    double acc = 0.0;
+    for (int h = 0; h < chunks; ++h)
+#pragma unroll 8
+        for (int i = w; i < n_r; i += 4) acc += (double)r[i] * (double)z[(i * chunks + h) * bq];
+    red[w][lane] = acc;
+    __syncthreads();
+    if (w == 0 && t < tot) c[t] = (float)(((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane]);
+}
+
 // Localised probes of eq. (14) on one geometry's nodes: row (age v, direction l = a n_az + b) holds
 // R[a][i] P[b][j] exp(-(s_k + age_v)^2 / (2 h^2)) / N_l
 __global__ void k_local_probe(const float* __restrict__ R, const float* __restrict__ P, const double* __restrict__ inv_n,
@@ -251,6 +400,22 @@ void cubic_bsplines(double u, int n, double* out)
             N[i] = v;
         }
     for (int a = 0; a < n; ++a) out[a] = N[a];
+}
+
+// Wave kernels up to 15 azimuth functions (they stay in registers): 264 vectors of the S_224 map on 64 x 96 x 64
+// nodes c -> x 91 us, x -> c 144 us, the block kernels 288 and 541.  From 17 on the block kernels, which hold them in LDS.
+struct SynWave {
+    int lk_log, chunks, nw;
+};
+bool syn_wave(const rtt_synthesis* s, int nvec, SynWave& w)
+{
+    if (!s->nb) return false;
+    w.chunks = (s->K + 63) / 64;
+    w.lk_log = 0;
+    while (w.lk_log < 6 && (1 << w.lk_log) < s->K) ++w.lk_log;
+    // few (node, vector) pairs: four waves share the cells of one
+    w.nw = (int64_t)s->n_r * nvec * w.chunks < 4096 ? 4 : 1;
+    return true;
 }
 
 int check_syn(const rtt_synthesis* s, int nvec)
@@ -365,9 +530,16 @@ extern "C" int synthesis_create(const rtt_geometry* g, int32_t gi, const rtt_syn
         up(&s->d_R, fR);
         up(&s->d_P, fP);
         up(&s->d_T, fT);
+        if (s->separable && nA <= 15) {
+            s->nb = nA <= 3 ? 4 : nA <= 7 ? 8 : 16;
+            std::vector<float> Pt((size_t)(gr.n_phi + 8) * s->nb, 0.f);
+            for (int j = 0; j < gr.n_phi; ++j)
+                for (int b = 0; b < nA; ++b) Pt[(size_t)j * s->nb + b] = fP[(size_t)b * gr.n_phi + j];
+            up(&s->d_Pt, Pt);
+        }
     }
     if (e != hipSuccess) {
-        for (float* p : {s->d_Q, s->d_R, s->d_P, s->d_T})
+        for (float* p : {s->d_Q, s->d_R, s->d_P, s->d_T, s->d_Pt})
             if (p) (void)hipFree(p);
         s->magic = 0;
         delete s;
@@ -382,7 +554,7 @@ extern "C" int synthesis_free(rtt_synthesis* s)
     if (!s) return RTT_OK;
     if (!valid_syn(s)) return fail(RTT_EINVAL, "invalid synthesis handle");
     (void)hipSetDevice(s->device);
-    for (float* p : {s->d_Q, s->d_R, s->d_P, s->d_T})
+    for (float* p : {s->d_Q, s->d_R, s->d_P, s->d_T, s->d_Pt})
         if (p) (void)hipFree(p);
     s->ws.release();
     s->magic = 0;
@@ -407,6 +579,21 @@ extern "C" int synth_expand(const rtt_synthesis* s, const float* c, float* x, in
     if (!c || !x) return fail(RTT_EINVAL, "NULL data pointer");
     hipStream_t st = (hipStream_t)stream;
     RTT_HIP(hipSetDevice(s->device));
+    SynWave w;
+    if (s->separable && syn_wave(s, nvec, w)) {
+        const dim3 grid((unsigned)s->n_r, (unsigned)nvec, (unsigned)w.chunks);
+        const size_t lds = sizeof(float) * (size_t)s->n_az * s->n_temporal;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(64 * w.nw), lds, st, s->d_R, s->d_Pt, s->d_T, s->n_radial, s->n_az,
+                               s->n_temporal, s->n_r, s->n_phi, s->K, w.lk_log, c, x, s->n_cols);
+        };
+        if (w.lk_log == 6)
+            s->nb == 4 ? go(k_synth_expand_wave<4, true>) : s->nb == 8 ? go(k_synth_expand_wave<8, true>) : go(k_synth_expand_wave<16, true>);
+        else
+            s->nb == 4 ? go(k_synth_expand_wave<4, false>) : s->nb == 8 ? go(k_synth_expand_wave<8, false>) : go(k_synth_expand_wave<16, false>);
+        RTT_HIP(hipGetLastError());
+        return RTT_OK;
+    }
     if (s->separable) {
         const size_t lds = sizeof(float) * ((size_t)s->d + (size_t)s->n_radial * s->n_az * s->K + (size_t)s->n_az * s->K);
         hipLaunchKernelGGL(k_synth_expand, dim3((unsigned)s->n_r, (unsigned)nvec), dim3(256), lds, st, s->d_R, s->d_P,
@@ -430,6 +617,27 @@ extern "C" int synth_project(const rtt_synthesis* s, const float* x, float* c, i
     if (!c || !x) return fail(RTT_EINVAL, "NULL data pointer");
     hipStream_t st = (hipStream_t)stream;
     RTT_HIP(hipSetDevice(s->device));
+    SynWave w;
+    if (s->separable && syn_wave(s, nvec, w)) {
+        const int bq = s->n_az * s->n_temporal;
+        float* Z = (float*)s->ws.get("part", sizeof(float) * (size_t)nvec * s->n_r * w.chunks * bq);
+        if (!Z) return fail(RTT_ENOMEM, "synth_project scratch");
+        const dim3 grid((unsigned)s->n_r, (unsigned)nvec, (unsigned)w.chunks);
+        const size_t lds = sizeof(float) * (size_t)w.nw * s->nb * 68;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(64 * w.nw), lds, st, s->d_Pt, s->d_T, s->n_az, s->n_temporal, s->n_r,
+                               s->n_phi, s->K, w.lk_log, x, s->n_cols, Z);
+        };
+        if (w.lk_log == 6)
+            s->nb == 4 ? go(k_synth_project_wave<4, true>) : s->nb == 8 ? go(k_synth_project_wave<8, true>) : go(k_synth_project_wave<16, true>);
+        else
+            s->nb == 4 ? go(k_synth_project_wave<4, false>) : s->nb == 8 ? go(k_synth_project_wave<8, false>) : go(k_synth_project_wave<16, false>);
+        const int64_t tot = (int64_t)s->d * nvec;
+        hipLaunchKernelGGL(k_synth_radial_sum, dim3((unsigned)((tot + 63) / 64)), dim3(256), 0, st, s->d_R, Z,
+                           s->n_radial, bq, s->n_r, w.chunks, tot, c);
+        RTT_HIP(hipGetLastError());
+        return RTT_OK;
+    }
     if (s->separable) {
         float* part = (float*)s->ws.get("part", sizeof(float) * (size_t)nvec * s->n_r * s->d);
         if (!part) return fail(RTT_ENOMEM, "synth_project scratch");

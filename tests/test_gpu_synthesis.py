@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import synth
-from tinygeo import tiny_geometry
+from tinygeo import tiny_geometry, tiny_grid
 
 pytestmark = pytest.mark.gpu
 
@@ -122,3 +122,28 @@ def test_age_fisher_on_the_kerr_128_workload(gpu_lib):
     W = oracle.age_fisher(geo, ages, h=3.0)
     for i, a in enumerate(ages):
         assert rel(M[int(a) // 4], W[i]) < 1e-5
+
+
+@pytest.mark.parametrize("n_phi,n_hat,m_max,n_temporal,nvec",
+                         [(5, 4, 0, 1, 1), (7, 5, 1, 3, 3), (9, 33, 2, 4, 1), (12, 64, 3, 8, 70), (10, 65, 3, 6, 2),
+                          (16, 130, 4, 5, 3), (21, 31, 7, 3, 2), (24, 20, 8, 2, 2)])
+def test_synthesis_at_the_edges_of_its_kernels(gpu_lib, n_phi, n_hat, m_max, n_temporal, nvec):
+    """Lane layouts of the wave kernels (a power of two of hats and beside it, several chunks), 3/7/15
+    azimuth functions and the block kernels from 17 on, one and four waves a node.  Chains of at most
+    n_hat + n_phi + n_az + n_temporal FP32 additions: 2 sqrt(chain) 2^-24 relative, far below 1e-5."""
+    import torch
+    rtt = gpu_lib
+    n_r = 64 if nvec == 70 else 3
+    kw = dict(n_frames=2, n_r=n_r, n_phi=n_phi, delay_hi=2.0)
+    extra = n_hat - tiny_grid(n_orders=1, extra_hats=0, **kw).n_hat
+    geo = tiny_geometry(seed=43, rays=(3,), extra_hats=extra, **kw)
+    assert extra >= 0 and geo.grid.n_hat == n_hat
+    G = rtt.Geometry(geo)
+    S = rtt.Synthesis(G, 0, n_radial=4, m_max=m_max, n_temporal=n_temporal)
+    Q = oracle.synthesis_matrix(geo.grid, n_radial=4, m_max=m_max, n_temporal=n_temporal)
+    rng = np.random.default_rng(44)
+    c = rng.standard_normal((nvec, S.d)).astype(np.float32)
+    x = rng.standard_normal((nvec, S.n_cols)).astype(np.float32)
+    assert rel(S.expand(to_dev(c)).cpu().numpy(), c @ Q.T) < 1e-5
+    assert rel(S.project(to_dev(x)).cpu().numpy(), x @ Q) < 1e-5
+    torch.cuda.synchronize()
