@@ -1,11 +1,13 @@
 // Age-localised probes and historical reach (Sec. 3.3 eq. (10)-(13), Sec. 3.5 eq. (17), Sec. 4.4
 // eq. (29)-(30), Sec. 6.5 eq. (35)).
 //
-// age_information builds the probes q_a on the coefficient nodes (flat in space, a Gaussian of
-// width h in source time, unit L2 norm over the annulus), applies A to a block of them with the
-// operator kernels, and reduces the squared responses per (age, geometry, order) -- or, through an
-// order mixer, the squared mixed responses weighted by the propagated inverse variances -- in
-// FP64.  The threshold statistics (age_window, age_reach) are host arithmetic on those numbers.
+// age_information: the probes q_a are flat in space and a Gaussian of width h in source time, with unit
+// L2 norm over the annulus.  Per (age, geometry, order) the squared response of a ray is its squared
+// weight times a sum over frames that depends on its hat origin and fraction alone; those sums come from
+// tables of windowed sums (k_age_windows).  Through an order mixer the responses meet before they are
+// squared: there the probes are set on the coefficient nodes, A is applied to a block of them with the
+// operator kernels, and the squared mixed responses, weighted by the propagated inverse variances, are
+// reduced in FP64.  The threshold statistics (age_window, age_reach) are host arithmetic on those numbers.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -29,6 +31,117 @@ __global__ void k_age_probe(float* __restrict__ X, int64_t ldx, int64_t col_off,
     const int v = blockIdx.y;
     const double t = s0 + dt_src * (double)(c % K) + ages[v];
     X[(int64_t)v * ldx + col_off + c] = (float)(exp(-t * t / (2.0 * h * h)) * inv_norm);
+}
+
+// A probe is flat in space, so a ray of weight w (the sum of its four bilinear ones) at hat origin k and
+// fraction th answers w ((1 - th) g[k] + th g[k + 1]) in a frame, and the frames of one residue f mod Q have
+// the same fraction and origins P apart.  Their squares sum to
+//   w^2 ((1 - th)^2 W(k) + 2 th (1 - th) C(k) + th^2 W(k + 1)),
+//   W(k) = sum_{t < n} g[k + tP]^2,  C(k) = sum_{t < n} g[k + tP] g[k + tP + 1]   (g = 0 outside the hats),
+// all terms non-negative: nothing cancels.  k_age_windows tabulates W and C (FP64) for the origins that occur,
+// for n = n0 and n0 - 1 (class 0 and 1), a thread a row of one age.  A ray and age then cost three table reads instead of n_frames
+// rows of the operator: 64 ages of 128^2 rays x 128 frames 388 us (probes, A, dots through memory) -> 55 us a call, 22 of kernels.
+__global__ __launch_bounds__(256) void k_age_windows(int K, int P, int n0, int c0, int lo, int rows, double s0, double dt_src,
+                                                     const double* __restrict__ ages, double h, double inv_norm,
+                                                     int64_t ldv, double* __restrict__ tab)
+{
+    extern __shared__ double g[];   // [K]: FP64, so that an age far in the tail keeps its digits
+    const int v = blockIdx.x;
+    for (int k = threadIdx.x; k < K; k += blockDim.x) {
+        const double t = s0 + dt_src * (double)k + ages[v];
+        g[k] = exp(-t * t / (2.0 * h * h)) * inv_norm;
+    }
+    __syncthreads();
+    const int row = blockIdx.y * blockDim.x + threadIdx.x, cls = c0 + blockIdx.z;
+    if (row >= rows) return;
+    const int64_t k = lo + row, n = n0 - cls;   // k <= K - 1
+    const int64_t t0 = k >= -1 ? 0 : (-k - 1 + P - 1) / P, t1 = min(n, (K - 1 - k) / P + 1);
+    double w = 0.0, c = 0.0;
+    for (int64_t t = t0; t < t1; ++t) {
+        const int q = (int)(k + t * P);   // -1 <= q < K
+        const double a = q >= 0 ? g[q] : 0.0, b = q + 1 < K ? g[q + 1] : 0.0;
+        w += a * a;
+        c += a * b;
+    }
+    double* o = tab + ((int64_t)cls * rows + row) * 2 * ldv + v;
+    o[0] = w;
+    o[ldv] = c;
+}
+
+// one (geometry, order): its records in data-row order, and its partial sums
+struct AgeSeg {
+    int64_t ray, n_rays;
+    int32_t per, nsplit;   // rays of a block, blocks
+    int64_t part;          // first partial sum
+};
+
+// Lanes are ages, a ray is uniform over the wave (its record is a scalar load); the four waves of a block take
+// every fourth ray of its slice, four at a time so that twelve table reads are in flight.
+__global__ __launch_bounds__(256) void k_age_energy(const FwdRec* __restrict__ recs, const AgeSeg* __restrict__ segs,
+                                                    const double* __restrict__ tab, int rows, int lo, int P, int Q,
+                                                    int F, int nv, int64_t ldv, double* __restrict__ part)
+{
+    __shared__ double red[4][64];
+    const AgeSeg sg = segs[blockIdx.z];
+    if ((int)blockIdx.x >= sg.nsplit) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int v = min((int)blockIdx.y * 64 + lane, nv - 1);
+    const int64_t r0 = sg.ray + (int64_t)blockIdx.x * sg.per;
+    const int64_t r1 = min(sg.ray + sg.n_rays, r0 + sg.per);
+    double acc = 0.0;
+    for (int64_t rb = r0 + wave; rb < r1; rb += 16) {
+        for (int q = 0; q < Q; ++q) {
+            const int step = (int)((int64_t)q * P / Q);
+            const double frac = (double)((int64_t)q * P % Q) / (double)Q;
+            const double* __restrict__ tq = tab + (q < F % Q ? 0 : (int64_t)rows * 2 * ldv) + v;
+            double t0[4], t1[4], t2[4], th[4], w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const FwdRec& f = recs[min(rb + 4 * u, r1 - 1)];
+                th[u] = (double)f.th0 + frac;
+                const int carry = th[u] >= 1.0 ? 1 : 0;
+                th[u] -= (double)carry;
+                w[u] = rb + 4 * u < r1 ? ((double)f.b00 + (double)f.b11) + ((double)f.b10 + (double)f.b01) : 0.0;
+                const int64_t i = (int64_t)f.k0 + step + carry - lo;   // rows outside the table are zero
+                const bool in0 = i >= 0 && i < rows, in1 = i >= -1 && i + 1 < rows;
+                const int64_t i0 = in0 ? i : 0, i1 = in1 ? i + 1 : 0;
+                t0[u] = tq[i0 * 2 * ldv];
+                t1[u] = tq[(i0 * 2 + 1) * ldv];
+                t2[u] = tq[i1 * 2 * ldv];
+                t0[u] = in0 ? t0[u] : 0.0;
+                t1[u] = in0 ? t1[u] : 0.0;
+                t2[u] = in1 ? t2[u] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double p = 1.0 - th[u];
+                acc += w[u] * w[u] * (p * p * t0[u] + 2.0 * th[u] * p * t1[u] + th[u] * th[u] * t2[u]);
+            }
+        }
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0)   // part rows are ldv >= 64 ceil(nv / 64) long
+        part[(sg.part + blockIdx.x) * ldv + blockIdx.y * 64 + lane] =
+            ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+}
+
+__global__ __launch_bounds__(1024) void k_age_sum(const AgeSeg* __restrict__ segs, const double* __restrict__ part,
+                                                  int nseg, int nv, int64_t ldv, double* __restrict__ e)
+{
+    __shared__ double red[16][64];
+    const AgeSeg sg = segs[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * 64 + lane;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int t = wave; t < sg.nsplit; t += 16) acc += part[(sg.part + t) * ldv + v];
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && v < nv) {
+        for (int w = 1; w < 16; ++w) acc += red[w][lane];
+        e[v * nseg + blockIdx.y] = acc;
+    }
 }
 
 // W[v][i] = D[v][i] / var[i] (0 where var[i] == 0)
@@ -126,6 +239,87 @@ extern "C" int reference_response(const rtt_geometry* g, double* s_ref, void* st
     return RTT_OK;
 }
 
+namespace rtt {
+namespace {
+
+// The hat origins of member m whose windows meet the hats, and the terms of a window
+struct AgeWindow {
+    int64_t lo, rows, terms;
+};
+AgeWindow age_window_rows(const Member& m)
+{
+    const int64_t K = m.grid.n_hat, nt = m.grid.n_frames / m.Q;
+    const int64_t lo = std::max<int64_t>(m.k0_min, -nt * m.P - 1);
+    const int64_t hi = std::min<int64_t>(K - 1, m.k0_max + (int64_t)(m.Q - 1) * m.P / m.Q + 2);
+    return {lo, std::max<int64_t>(0, hi - lo + 1), std::min<int64_t>(nt + 1, K / m.P + 2)};
+}
+
+// ||A_{g,n} q_a||^2 for every age, geometry and order (host double [n_ages][G][8]) from the window tables
+int age_energies(const rtt_geometry* g, const double* ages, int n_ages, double h, double* energy, hipStream_t s)
+{
+    std::vector<AgeWindow> win;
+    std::vector<AgeSeg> segs;
+    int64_t parts = 0, max_rows = 1;
+    for (const Member& m : g->members) {
+        win.push_back(age_window_rows(m));
+        max_rows = std::max(max_rows, win.back().rows);
+        int64_t at = m.ray_begin;
+        for (int n = 0; n < 8; ++n) {
+            const int64_t len = n < m.grid.n_orders ? m.rays_per_order[n] : 0;
+            const int64_t per = std::max<int64_t>(32, (len + 511) / 512);   // at most 512 partial sums
+            segs.push_back({at, len, (int32_t)per, (int32_t)((len + per - 1) / per), parts});
+            parts += segs.back().nsplit;
+            at += len;
+        }
+    }
+    const int nseg = (int)segs.size();
+    // ages per pass: tables and partial sums stay under 256 MiB
+    const int64_t per_age = 8 * (4 * max_rows + parts);
+    const int64_t most = std::min<int64_t>(65535 / 64 * 64, (int64_t(1) << 28) / per_age / 64 * 64);
+    const int chunk = (int)std::min<int64_t>(((int64_t)n_ages + 63) / 64 * 64, std::max<int64_t>(64, most));
+    Workspace ws;
+    double* dages = (double*)ws.get("ages", sizeof(double) * (size_t)n_ages);
+    AgeSeg* dseg = (AgeSeg*)ws.get("seg", sizeof(AgeSeg) * segs.size());
+    double* tab = (double*)ws.get("tab", sizeof(double) * 4 * (size_t)max_rows * chunk);
+    double* part = (double*)ws.get("part", sizeof(double) * (size_t)std::max<int64_t>(1, parts) * chunk);
+    double* e = (double*)ws.get("e", sizeof(double) * (size_t)n_ages * nseg);
+    if (!dages || !dseg || !tab || !part || !e) return fail(RTT_ENOMEM, "age_information scratch");
+    RTT_HIP(hipMemcpyAsync(dages, ages, sizeof(double) * n_ages, hipMemcpyHostToDevice, s));
+    RTT_HIP(hipMemcpyAsync(dseg, segs.data(), sizeof(AgeSeg) * segs.size(), hipMemcpyHostToDevice, s));
+    for (int a0 = 0; a0 < n_ages; a0 += chunk) {
+        const int nv = std::min(chunk, n_ages - a0);
+        const unsigned vb = (unsigned)((nv + 63) / 64);
+        for (size_t gi = 0; gi < g->members.size(); ++gi) {
+            const Member& m = g->members[gi];
+            int splits = 0;
+            for (int n = 0; n < 8; ++n) splits = std::max(splits, segs[8 * gi + n].nsplit);
+            if (splits == 0) continue;
+            const AgeWindow& w = win[gi];
+            const int F = m.grid.n_frames, n0 = F / m.Q + 1;   // class 0: the residues below F mod Q
+            const int c0 = F % m.Q ? 0 : 1;
+            if (w.rows > 0)
+                hipLaunchKernelGGL(k_age_windows, dim3((unsigned)nv, (unsigned)((w.rows + 255) / 256), (unsigned)(2 - c0)),
+                                   dim3(256), sizeof(double) * m.grid.n_hat, s, m.grid.n_hat, m.P, n0, c0, (int)w.lo,
+                                   (int)w.rows, m.grid.s0, m.grid.dt_src, dages + a0, h, 1.0 / probe_norm(m.grid, h),
+                                   (int64_t)chunk, tab);
+            hipLaunchKernelGGL(k_age_energy, dim3((unsigned)splits, vb, (unsigned)m.grid.n_orders), dim3(256), 0, s,
+                               g->d_fwd_row, dseg + 8 * gi, tab, (int)w.rows, (int)w.lo, m.P, m.Q, F, nv,
+                               (int64_t)chunk, part);
+        }
+        hipLaunchKernelGGL(k_age_sum, dim3(vb, (unsigned)nseg), dim3(1024), 0, s, dseg, part, nseg, nv, (int64_t)chunk,
+                           e + (int64_t)a0 * nseg);
+        RTT_HIP(hipGetLastError());
+    }
+    std::vector<double> he((size_t)n_ages * nseg);
+    RTT_HIP(hipMemcpyAsync(he.data(), e, sizeof(double) * he.size(), hipMemcpyDeviceToHost, s));
+    RTT_HIP(hipStreamSynchronize(s));
+    std::memcpy(energy, he.data(), sizeof(double) * he.size());
+    return RTT_OK;
+}
+
+}  // namespace
+}  // namespace rtt
+
 extern "C" int age_information(const rtt_geometry* g, const double* ages, int32_t n_ages, double h,
                                const rtt_mixer* mixer, const float* var, double* energy, void* stream)
 {
@@ -143,6 +337,14 @@ extern "C" int age_information(const rtt_geometry* g, const double* ages, int32_
     if (n_ages == 0) return RTT_OK;
     hipStream_t s = (hipStream_t)stream;
     RTT_HIP(hipSetDevice(g->device));
+    // Window tables where a ray costs at most 24 reads an age (3 Q), the hats fit 64 KB of LDS and the tables
+    // 128 MiB for 64 ages; the responses themselves past that, and for mixers.
+    bool tables = !mixer;
+    for (const Member& m : g->members) {
+        const AgeWindow w = age_window_rows(m);
+        tables = tables && m.Q <= 8 && m.grid.n_hat <= 8192 && w.rows <= 65536 && w.terms <= 4096;
+    }
+    if (tables) return age_energies(g, ages, n_ages, h, energy, s);
     // segments: (geometry, order) row blocks, or every geometry's mixed rows
     std::vector<int64_t> hseg;
     if (!mixer) {

@@ -148,3 +148,29 @@ def test_age_information_of_the_mechanism_arms(gpu_lib, arm):
     E = rtt.age_information(G, ages, h=3.0)
     assert relerr(E[:, 0, :3].sum(axis=1), oracle.age_energy(geo, ages, arm="resolved")) < TOL
     assert relerr(E[:, 0, 0], oracle.age_energy(geo, ages, arm="direct")) < TOL
+
+
+@pytest.mark.parametrize("n_frames,dt_obs,extra_hats,n_ages",
+                         [(1, 4.0, 1, 1), (7, 4.0, 1, 65), (7, 2.0, 1, 64), (8, 2.0, -3, 3), (10, 6.0, 1, 5),
+                          (5, 8.0, -4, 130), (3, 0.5, 1, 2), (11, 4.0 / 9.0, 1, 3)])
+def test_age_information_by_windows_of_frames(gpu_lib, n_frames, dt_obs, extra_hats, n_ages):
+    """Every order's energy at whole, half and 3/2 steps of the hats, fewer frames than a cycle, hats that end
+    before the frames do, one age to three groups of 64, and a cycle past the tables (9 frames).  FP32 hat
+    values, weights and fractions enter a square: 2 (3 2^-24 + the fraction's 2^-24 times at most 10 of slope)
+    is 1.6e-6 of the order's largest energy."""
+    rtt = gpu_lib
+    geos = [tiny_geometry(seed=95 + i, rays=r, n_frames=n_frames, dt_obs=dt_obs, extra_hats=extra_hats,
+                          delay_hi=30.0) for i, r in enumerate([(70, 0, 33), (1, 5)])]
+    G = rtt.Geometry(geos)
+    ages = np.linspace(-8.0, 70.0, n_ages)
+    say("case age windows", n_frames, dt_obs, extra_hats, n_ages)
+    E = rtt.age_information(G, ages, h=3.0)
+    for g, geo in enumerate(geos):
+        Y = oracle.forward(geo, oracle.age_probes(geo.grid, ages, 3.0)).reshape(n_ages, -1)
+        at = 0
+        for n, m in enumerate(geo.maps):
+            end = at + m.n_rays * n_frames
+            want = np.einsum("ar,ar->a", Y[:, at:end], Y[:, at:end])
+            assert np.max(np.abs(E[:, g, n] - want), initial=0.0) <= 2e-6 * np.max(want), (g, n)
+            at = end
+        assert np.all(E[:, g, geo.grid.n_orders:] == 0.0)
