@@ -789,7 +789,7 @@ int combine(Workspace& ws, const float* C, int K, int M, const float* Y, int64_t
         RTT_HIP(hipGetLastError());
         return RTT_OK;
     }
-    // All row blocks over one pass of Y (288 x 288 upper over 1.55M columns 1.66 against 1.81 ms; 96 x 96 over
+    // All row blocks over one pass of Y (288 x 288 upper over 1.55M columns 1.56 against 1.81 ms; 96 x 96 over
     // 393k 85 us both; 160 over 260k 130 against 139; 64 x 64 over 5000 12 against 15) wherever its 32-bit
     // column offsets reach.
     if (K >= 16 && M > 32 && (8 * ldy + L) * 4 < ((int64_t)1 << 32)) {

@@ -16,8 +16,9 @@
 // combine_wide: Out = beta Out + C^T Y with FP32 matrix instructions.  A wave owns 32 columns and up to 9 row
 // blocks of Out; its columns of Y go from memory to registers, 16 rows two steps ahead, and C comes through
 // LDS in fragment order.  Y is read once, against three passes with 4 row blocks each.  288 x 288 upper
-// triangular over 1.55M columns: 1.81 -> 1.66 ms (0.56 -> 0.48 over 393k), bound by the FP32 matrix rate
-// (143 GFLOP, 0.93 ms at the rate of a large library product).  The bf16 split of the Gram form was measured
+// triangular over 1.55M columns: 1.81 -> 1.56 ms (0.56 -> 0.45 over 393k; 1.66 and 0.48 with the wait for the
+// next C in front of a step's products, which left the rows of Y one step to arrive), bound by the FP32 matrix
+// rate (143 GFLOP, 0.93 ms at the rate of a large library product) and the 3.6 GB moved (0.76 ms).  The bf16 split of the Gram form was measured
 // here too (1.37 ms) and dropped: its matrix instructions cut the small terms of a step off towards zero where
 // one term is much larger (R^-1 of a second pass: 1 beside 1e-4), as if the coefficients were off by up to
 // 1.5e-8, and the TSVD estimate at rank 256 lost a digit (1e-5 against 1.5e-6).
@@ -248,9 +249,10 @@ __global__ __launch_bounds__(SW * 64, 2) void k_combine_wide(const f4v* __restri
     // uniform row address plus a 32-bit offset per lane (half 1 takes the rows 8 .. 15 of a step)
     const uint32_t yoff = (uint32_t)(((int64_t)half * 8 * ldy + lc) * 4);
     const int kend = upper ? min(K, m0 + MG * 32) : K;
+    const int klast = (kend - 1) & ~15;
     f4v cr[NC];
     auto load_c = [&](int k0) {
-        const f4v* __restrict__ p = frag + ((int64_t)(k0 >> 4) * nb + g0) * 2 * 64;
+        const f4v* __restrict__ p = frag + ((int64_t)(min(k0, klast) >> 4) * nb + g0) * 2 * 64;
 #pragma unroll
         for (int q = 0; q < NC; ++q) cr[q] = p[min(tid + q * SW * 64, NU - 1)];
     };
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(SW * 64, 2) void k_combine_wide(const f4v* __restri
     };
     float ya[8], yb[8];
     auto load_y = [&](int k0, float* y) {
-        const char* __restrict__ p = (const char*)(Y + (int64_t)min(k0, K - 16) * ldy) + yoff;
+        const char* __restrict__ p = (const char*)(Y + (int64_t)min(min(k0, klast), K - 16) * ldy) + yoff;
 #pragma unroll
         for (int t = 0; t < 8; ++t) y[t] = *(const float*)(p + (int64_t)t * ldy * 4);
     };
@@ -269,15 +271,17 @@ __global__ __launch_bounds__(SW * 64, 2) void k_combine_wide(const f4v* __restri
 #pragma unroll
     for (int g = 0; g < MG; ++g) acc[g] = (f16v){};
     int buf = 0;
-    // one 16-row step: y holds its rows of Y, then receives those two steps ahead
+    // One 16-row step: y holds its rows of Y, then receives those two steps ahead.  The next step's C goes to LDS
+    // at the end: the wait for it covers the loads that are older, the rows of Y of the next step, and not the
+    // ones issued here, which have two steps to arrive.  Loads past the last step repeat it (no branch around
+    // a load: the compiler would wait for all of them at the join).
     auto step = [&](int k0, float* y) {
         float b[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) b[t] = y[t];
-        if (k0 + 32 < kend) load_y(k0 + 32, y);
-        if (k0 + 16 < kend) store_c(buf ^ 1);
-        if (k0 + 32 < kend) load_c(k0 + 32);
-        const int gmin = upper && k0 > m0 ? (k0 - m0) >> 5 : 0;   // row blocks that end before k0: exact zeros
+        load_y(k0 + 32, y);
+        // row blocks that end before k0 are exact zeros; a step past the last does nothing
+        const int gmin = k0 >= kend ? MG : upper && k0 > m0 ? (k0 - m0) >> 5 : 0;
 #pragma unroll
         for (int g = 0; g < MG; ++g)
             if (g >= gmin) {
@@ -286,18 +290,20 @@ __global__ __launch_bounds__(SW * 64, 2) void k_combine_wide(const f4v* __restri
                 for (int t = 0; t < 8; ++t)
                     acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(t < 4 ? a0[t & 3] : a1[t & 3], b[t], acc[g], 0, 0, 0);
             }
+        store_c(buf ^ 1);
+        load_c(k0 + 32);
         __syncthreads();
         buf ^= 1;
     };
     load_c(0);
     load_y(0, ya);
-    if (16 < kend) load_y(16, yb);
+    load_y(16, yb);
     store_c(0);
-    if (16 < kend) load_c(16);
+    load_c(16);
     __syncthreads();
     for (int k0 = 0; k0 < kend; k0 += 32) {
         step(k0, ya);
-        if (k0 + 16 < kend) step(k0 + 16, yb);
+        step(k0 + 16, yb);
     }
     if (l >= L) return;
 #pragma unroll
