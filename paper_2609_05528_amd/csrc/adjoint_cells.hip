@@ -34,6 +34,7 @@ struct CellArgs {
     int nvec;
     const float* y;
     float* x;
+    float* x2;                // both parities in one launch: the odd rows' share (as x), or NULL
     int64_t y_stride, x_stride;
     uint32_t mask;
 };
@@ -77,7 +78,8 @@ __global__ __launch_bounds__(W * WAVE, 4) void k_adjoint_cells(CellArgs a)
     const int lin = (int)(bx * per + min(bx, rem) + bi);
     const int kch = lin % a.kchunks;
     const int tb = lin / a.kchunks;
-    const int ci = a.pr + 2 * (tb / a.cgroups);
+    const int pr = a.x2 ? (int)blockIdx.z : a.pr;
+    const int ci = pr + 2 * (tb / a.cgroups);
     const int jb = (tb % a.cgroups) * (G - 1);       // first column of the workgroup
     const int grp = wave / S, part = wave % S;
     const int jo = jb + grp - 1;                     // this wave's base column
@@ -248,8 +250,8 @@ __global__ __launch_bounds__(W * WAVE, 4) void k_adjoint_cells(CellArgs a)
             }
             const int k = kc - H + lane + WAVE * v;
             if (k < kc || k >= a.K || ci + r >= a.n_r) continue;
-            float* __restrict__ p = a.x + (int64_t)(v0 + u) * a.x_stride + ((int64_t)(ci + r) * a.n_phi + jo) * a.K + k;
-            *p = a.pr == 0 ? left + right : *p + (left + right);
+            float* __restrict__ p = (pr && a.x2 ? a.x2 : a.x) + (int64_t)(v0 + u) * a.x_stride + ((int64_t)(ci + r) * a.n_phi + jo) * a.K + k;
+            *p = pr == 0 || a.x2 ? left + right : *p + (left + right);
         }
     }
 }
@@ -267,6 +269,13 @@ void cells_launch(CellArgs a, hipStream_t s)
     constexpr int C = cells_chunk<Q, V, HALO>(), G = W / S;
     a.kchunks = (a.K + C - 1) / C;
     a.cgroups = (a.n_phi + G - 2) / (G - 1);
+    if (a.x2) {
+        hipLaunchKernelGGL((k_adjoint_cells<Q, V, NB, NVW, W, S, HALO>),
+                           dim3((unsigned)((a.n_r + 1) / 2) * (unsigned)a.cgroups * (unsigned)a.kchunks,
+                                (unsigned)((a.nvec + NVW - 1) / NVW), 2),
+                           dim3(W * WAVE), 0, s, a);
+        return;
+    }
     for (a.pr = 0; a.pr < 2; ++a.pr) {
         // the even rows take the last row too (it has no rays of its own but may have to be cleared)
         const int rows = a.pr == 0 ? (a.n_r + 1) / 2 : (a.n_r - 1) / 2;
@@ -329,7 +338,7 @@ bool adjoint_cells_ok(const Member& m)
 }
 
 int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec, int64_t y_stride,
-                         int64_t x_stride, uint32_t mask, hipStream_t s)
+                         int64_t x_stride, uint32_t mask, hipStream_t s, float* x2)
 {
     CellArgs a{};
     a.rec = g->d_fwd + m.ray_begin;
@@ -341,6 +350,7 @@ int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y,
     a.nvec = nvec;
     a.y = y;
     a.x = x;
+    a.x2 = x2;
     a.y_stride = y_stride;
     a.x_stride = x_stride;
     a.mask = mask;

@@ -3475,6 +3475,13 @@ static void rows_dispatch(const RowsArgs& a, int nvec, hipStream_t s)
     }
 }
 
+// the base-cell kernel reads these rows: aligned frame pairs at Q = 2
+static bool cells_rows_ok(const Member& m, const float* y, int nvec, int64_t y_stride)
+{
+    const bool fpair = m.Q == 1 || ((m.grid.n_frames % 2) == 0 && (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (y_stride % 2) == 0));
+    return fpair && adjoint_cells_ok(m);
+}
+
 int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec,
                    int64_t y_stride, int64_t x_stride, uint32_t mask, hipStream_t s, int variant)
 {
@@ -3534,8 +3541,7 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
     }
     // base cells: frame pairs at Q = 2; else the single-row lane-shifted form
     if (variant == 23) {
-        const bool fpair = m.Q == 1 || ((m.grid.n_frames % 2) == 0 && (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (y_stride % 2) == 0));
-        if (fpair && adjoint_cells_ok(m)) return launch_adjoint_cells(g, m, y, x, nvec, y_stride, x_stride, mask, s);
+        if (cells_rows_ok(m, y, nvec, y_stride)) return launch_adjoint_cells(g, m, y, x, nvec, y_stride, x_stride, mask, s);
         variant = nvec >= 2 ? 17 : 16;
     }
     if ((variant == 11 || variant >= 14) && !visit_fits(m.n_rows, m.n_cols, y_stride, x_stride, 1)) variant = 2;
@@ -3668,6 +3674,16 @@ int apply_op(const rtt_geometry* g, int member, bool adjoint, const float* in, f
         }
     }
     return RTT_OK;
+}
+
+bool adjoint_parts(const rtt_geometry* g, const float* y, float* x, float* x2, int nvec, uint32_t mask, hipStream_t s,
+                   int* rc)
+{
+    if (g->members.size() != 1 || nvec == 0) return false;
+    const Member& m = g->members[0];
+    if (adjoint_variant_for(g, m, nvec) != 23 || !adjoint_variant_ok(m, 23) || !cells_rows_ok(m, y, nvec, g->n_rows)) return false;
+    *rc = launch_adjoint_cells(g, m, y, x, nvec, g->n_rows, g->n_cols, effective_mask(m, mask), s, x2);
+    return true;
 }
 
 int whole_operator_launches(const rtt_geometry* g, bool adjoint)

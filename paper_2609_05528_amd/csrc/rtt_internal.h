@@ -151,7 +151,7 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
 // A^T over base cells (adjoint_cells.hip); data rows must be even and 8-byte aligned when Q = 2
 bool adjoint_cells_ok(const Member& m);
 int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec, int64_t y_stride,
-                         int64_t x_stride, uint32_t mask, hipStream_t s);
+                         int64_t x_stride, uint32_t mask, hipStream_t s, float* x2 = nullptr);
 int n_adjoint_variants();
 int n_apply_variants();
 const char* adjoint_variant_name(int v);
@@ -172,6 +172,11 @@ uint32_t effective_mask(const Member& m, uint32_t mask);
 // block-diagonal operator (full-length vectors).
 int apply_op(const rtt_geometry* g, int member, bool adjoint, const float* in, float* out, int nvec,
              uint32_t mask, hipStream_t s, bool shared_x = false);
+// A^T of a handle whose call takes the base cells, in one launch: x receives the even cell rows' share and x2
+// the odd ones' (A^T y = x + x2, the bits of apply_op; x2 only where odd rows reach: zeroed by the caller).
+// false: nothing was done.
+bool adjoint_parts(const rtt_geometry* g, const float* y, float* x, float* x2, int nvec, uint32_t mask, hipStream_t s,
+                   int* rc);
 // kernel launches one whole-operator op_apply (or op_apply_adjoint) call makes with the current
 // variants and launch modes (for one vector)
 int whole_operator_launches(const rtt_geometry* g, bool adjoint);

@@ -18,7 +18,7 @@
 namespace rtt {
 
 // The vector work of an iteration in three kernels (nine before: 20 iterations at 256^2, one right-hand
-// side, 1.44 -> 1.00 ms, the launches of 4 to 5 us each being the cost).  Grid: (slices of a geometry's
+// side, 1.44 -> 1.00 ms, 0.81 with A^T in one launch; the launches of 4 to 5 us each being the cost).  Grid: (slices of a geometry's
 // column block, right-hand sides, geometries); a block takes one slice of one pair and leaves the FP64
 // partial of the pair's dot product, and the next kernel's blocks each add the pair's partials in the same
 // fixed order.  The residual norms and flags alternate between two buffers: every block of an iteration
@@ -92,9 +92,9 @@ __global__ __launch_bounds__(CG_T) void k_cg_init(const double* __restrict__ par
     }
 }
 
-// Ap += lambda p, partials of <p, Ap>
-__global__ __launch_bounds__(CG_T) void k_cg_pap(float* __restrict__ Ap, const float* __restrict__ p, float lam,
-                                                 const int64_t* __restrict__ seg, int64_t n, double* __restrict__ part)
+// Ap += Ap2 (when given) + lambda p, partials of <p, Ap>
+__global__ __launch_bounds__(CG_T) void k_cg_pap(float* __restrict__ Ap, const float* __restrict__ Ap2,
+                                                 const float* __restrict__ p, float lam, const int64_t* __restrict__ seg, int64_t n, double* __restrict__ part)
 {
     const CgPair c = cg_pair(seg, n);
     double acc = 0.0;
@@ -102,10 +102,9 @@ __global__ __launch_bounds__(CG_T) void k_cg_pap(float* __restrict__ Ap, const f
     for (int64_t i = c.off + c.l0 + threadIdx.x; i < c.off + c.l1; i += CG_T) {
         const float pv = p[i];
         float av = Ap[i];
-        if (lam != 0.f) {
-            av += lam * pv;
-            Ap[i] = av;
-        }
+        if (Ap2) av += Ap2[i];
+        if (lam != 0.f) av += lam * pv;
+        if (Ap2 || lam != 0.f) Ap[i] = av;
         acc += (double)pv * (double)av;
     }
     acc = cg_block_sum(acc);
@@ -235,10 +234,20 @@ extern "C" int ridge_solve(const rtt_geometry* g, const float* y, int32_t nrhs, 
         }
     }
     const int check_every = 8;
+    // Where A^T goes by base cells its two launches, the second of which adds to the first, become one that
+    // leaves two shares, and the kernel that follows adds them (256^2, one right-hand side: 24.4 -> 15.1 us a
+    // product, 20 iterations 1002 -> 814 us).
+    // (The buffer does not depend on the variant of the moment: a captured solve finds it whatever is pinned.)
+    float* Ap2 = nullptr;
+    if (G == 1 && adjoint_cells_ok(g->members[0])) Ap2 = (float*)ws.get("cg_ap2", sizeof(float) * (size_t)nrhs * n);
+    bool parts2 = Ap2 != nullptr;
+    if (parts2 && (rc = fill(Ap2, (int64_t)nrhs * n, 0.f, s))) return rc;
     while (it < maxit) {
         if ((rc = apply_op(g, -1, false, p, q, nrhs, mask, s))) return rc;
-        if ((rc = apply_op(g, -1, true, q, Ap, nrhs, mask, s))) return rc;
-        hipLaunchKernelGGL(k_cg_pap, grid, blk, 0, s, Ap, p, lambda, seg, n, pap_part);
+        rc = RTT_OK;
+        parts2 = parts2 && adjoint_parts(g, q, Ap, Ap2, nrhs, mask, s, &rc);
+        if (rc || (!parts2 && (rc = apply_op(g, -1, true, q, Ap, nrhs, mask, s)))) return rc;
+        hipLaunchKernelGGL(k_cg_pap, grid, blk, 0, s, Ap, parts2 ? Ap2 : nullptr, p, lambda, seg, n, pap_part);
         hipLaunchKernelGGL(k_cg_xr, grid, blk, 0, s, x, r, p, Ap, pap_part, rr, done, seg, n, pap, rr_part);
         hipLaunchKernelGGL(k_cg_p, grid, blk, 0, s, p, r, rr_part, rr, bb, pap, done, seg, n, tol2, rr_next, done_next);
         std::swap(rr, rr_next);

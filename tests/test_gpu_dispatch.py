@@ -105,3 +105,43 @@ def test_unpinned_batch_gives_the_same_bits_in_every_launch_mode_and_block(gpu_l
         for nv in (1, 2, 3, 9):
             assert torch.equal(rtt.op_apply(G, X[:nv].contiguous()), y[:nv]), (mode, nv)
             assert torch.equal(rtt.op_apply_adjoint(G, Y[:nv].contiguous()), x[:nv]), (mode, nv)
+
+
+@pytest.mark.parametrize("name", ["one_wave_ragged", "one_wave_7_columns", "two_rows_8_columns", "one_column",
+                                  "four_waves", "empty_cells", "half_steps", "half_steps_odd_rows"])
+def test_ridge_by_shares_of_the_cell_rows_matches_oracle(gpu_lib, name):
+    """The solver's one-launch adjoint (even and odd cell rows apart) on a handle pinned to the base cells,
+    and the two launches of a handle with another kernel, after the same iterations.  lambda = |A|^2: a
+    condition of 2, so three iterations carry the FP32 errors of six products, within TOL."""
+    rtt = gpu_lib
+    say("case ridge shares", name)
+    geo = tiny_geometry(seed=203, **CELLS[name])
+    rng = np.random.default_rng(4)
+    v = rng.standard_normal(geo.grid.n_cols)
+    for _ in range(8):
+        v = oracle.adjoint(geo, oracle.forward(geo, v / np.linalg.norm(v)))
+    lam = float(np.float32(np.linalg.norm(v)))
+    Y = to_dev(rng.standard_normal((3, geo.n_rows)))
+    y = Y.double().cpu().numpy()
+    for mask in (0, 1):
+        for kernel in ("visitc", "visitd"):
+            G = rtt.Geometry(geo)
+            G.set_variant(adjoint=rtt.variant_names(True).index(kernel))
+            X, _ = rtt.ridge_solve(G, Y, lam, tol=1e-12, maxit=3, async_mode=True, order_mask=mask)
+            for b in range(3):
+                want = three_iterations(geo, y[b], lam, mask or None)
+                assert rel(X[b].cpu().numpy(), want) <= TOL, (kernel, mask, b)
+
+
+def three_iterations(geo, y, lam, mask):
+    A = lambda x: oracle.forward(geo, x, order_mask=mask)  # noqa: E731
+    At = lambda q: oracle.adjoint(geo, q, order_mask=mask)  # noqa: E731
+    r = At(y)
+    x, p, rr = np.zeros_like(r), r.copy(), r @ r
+    for _ in range(3):
+        Ap = At(A(p)) + lam * p
+        a = rr / (p @ Ap)
+        x, r = x + a * p, r - a * Ap
+        new = r @ r
+        p, rr = r + new / rr * p, new
+    return x
