@@ -1198,11 +1198,16 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
             return;
         }
     }
-    if constexpr (VEC4 && Q == 1 && NB % 2 == 0) {
-        if ((F & 3) == 0 && (((uintptr_t)y) & 15) == 0) {
-            // rows of a multiple of 4 frames, 16-byte aligned: two rays per pass (lanes 0-31 ray j,
-            // lanes 32-63 ray j + 1), four frames per lane in one 16-byte store, the same values
-            // as the per-ray path below
+    if constexpr (Q == 1) {
+        static_assert(NB % 2 == 0, "two rays per pass");
+        if (F >= 4) {
+            // two rays per pass (lanes 0-31 ray j, lanes 32-63 ray j + 1), four frames per lane in one 16-byte
+            // store, the same values as the per-ray path below.  Rows may start at any float (global stores
+            // need 4-byte alignment only); the last lane of a row whose length is not a multiple of 4 moves
+            // back to end with it and writes the values of its neighbour again.  60 vectors on 64 x 64 cells,
+            // rows of 73, 81, 99 and 125 frames: 204, 93, 140 and 87 us by single floats, 154, 74, 102 and 70
+            // here.  (Without the non-temporal hint 235, 114, 149 and 89.)
+            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
             const bool hi = lane >= 32;
 #pragma unroll
             for (int j = 0; j < NB; j += 2) {
@@ -1212,15 +1217,16 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
                 const int k0 = hi ? rc[j + 1].k0 : rc[j].k0;
                 const bool o = hi ? on[j + 1] : on[j];
                 float* yr = y + (int64_t)(hi ? rc[j + 1].row : rc[j].row) * F;
-                for (int f = 4 * (lane & 31); f < F; f += 128) {
+                for (int q = 4 * (lane & 31); q < F; q += 128) {
+                    const int f = min(q, F - 4);
                     const float z0 = zat(k0 + f), z1 = zat(k0 + f + 1), z2 = zat(k0 + f + 2);
                     const float z3 = zat(k0 + f + 3), z4 = zat(k0 + f + 4);
-                    f4 v;
+                    f4u v;
                     v[0] = fmaf(th, z1 - z0, z0);
                     v[1] = fmaf(th, z2 - z1, z1);
                     v[2] = fmaf(th, z3 - z2, z2);
                     v[3] = fmaf(th, z4 - z3, z3);
-                    if (o) __builtin_nontemporal_store(v, (f4*)(yr + f));
+                    if (o) __builtin_nontemporal_store(v, (f4u*)(yr + f));
                 }
             }
             return;
@@ -1235,16 +1241,7 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
         const float th = rc[j].th0;
         const int k0 = rc[j].k0;
         float* yr = y + (int64_t)rc[j].row * F;
-        if (VEC4 && Q == 1) {
-            typedef float f2 __attribute__((ext_vector_type(2)));
-            for (int f = 2 * lane; f < F; f += 2 * WAVE) {
-                const float z0 = zat(k0 + f), z1 = zat(k0 + f + 1), z2 = zat(k0 + f + 2);
-                f2 v;
-                v[0] = fmaf(th, z1 - z0, z0);
-                v[1] = fmaf(th, z2 - z1, z1);
-                __builtin_nontemporal_store(v, (f2*)(yr + f));
-            }
-        } else if (VEC4) {
+        if (VEC4 && Q == 2) {
             const bool c1 = th >= 0.5f;
             const float th1 = c1 ? th - 0.5f : th + 0.5f;
             for (int g = lane; 4 * g < F; g += WAVE) {
@@ -2635,12 +2632,15 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     const int64_t F = m.grid.n_frames;
     if (m.grid.n_hat <= ABS_KMAX) {
         // Absolute hats.  Rows that end inside a 128-byte line leave staged and aligned when they are long
-        // enough to outweigh the lost gather reuse (60 vectors, 12 geometries of 64 x 64 cells: 134, 143
-        // and 151 frames 297, 138 and 394 us row-ordered against 370, 175 and 599; 125 frames 83 against
-        // 79, 160 frames 195 against 144).  One launch for all members serves one or two vectors (12
+        // enough to outweigh the lost gather reuse (60 vectors on 64 x 64 cells: 134, 143 and
+        // 151 frames 301, 144 and 396 us row-ordered against 368, 161 and 548; 125 frames 104 against 66, 160
+        // frames, whole lines, 213 against 160).  One launch for all members serves one or two vectors (12
         // geometries: 59 against 71 us; 8 vectors 438 against 366).
         if (g->members.size() > 1 && nvec <= 2) return 11;
-        return m.Q == 1 && F >= 130 && F % 32 != 0 && F <= lean_fcmax(1) ? 14 : 11;
+        // So do rows of whole lines that a member's place in the data vector moves off them (the sixth of the
+        // 12, 160 frames: 214 us row-ordered, 257 by cells; 160 where its lines are whole).
+        const bool ragged = F % 32 != 0 || (g->members.size() > 1 && (m.row_offset % 32 != 0 || g->n_rows % 32 != 0));
+        return m.Q == 1 && F >= 130 && ragged && F <= lean_fcmax(1) ? 14 : 11;
     }
     // More than 128 hats: the lean products; records in data-row order where rows share lines with their
     // neighbours (200^2 x 150 frames, 64 vectors: 310 against 365 us; 360^2 x 300, 8 vectors: 285 against

@@ -107,6 +107,28 @@ def test_unpinned_batch_gives_the_same_bits_in_every_launch_mode_and_block(gpu_l
             assert torch.equal(rtt.op_apply_adjoint(G, Y[:nv].contiguous()), x[:nv]), (mode, nv)
 
 
+@pytest.mark.parametrize("frames", [1, 2, 3, 4, 5, 7, 63, 125, 126, 127, 128, 129, 131, 259])
+def test_forward_of_absolute_hats_at_every_row_length(gpu_lib, frames):
+    """Four frames a store at any row start: rows shorter than a store, ragged ends, one and two more passes,
+    and nothing written beside the block."""
+    import dataclasses
+    import torch
+    rtt = gpu_lib
+    say("case row length", frames)
+    geo = tiny_geometry(seed=204, rays=(37, 6), n_r=4, n_phi=6, n_frames=frames)
+    geo.grid = dataclasses.replace(geo.grid, n_hat=min(geo.grid.n_hat, 128))   # later frames lie outside the hats
+    G = rtt.Geometry(geo)
+    G.set_variant(apply=rtt.variant_names(False).index("abs4"))
+    X = to_dev(np.random.default_rng(5).standard_normal((2, G.n_cols)))
+    ref = oracle.forward(geo, X.double().cpu().numpy())
+    for pad in (0, 1, 2, 3):   # every phase of the block's start
+        buf = torch.full((2 * G.n_rows + 16,), 7.0, device="cuda")
+        out = buf[4 + pad:4 + pad + 2 * G.n_rows].view(2, G.n_rows)
+        rtt.op_apply(G, X, y=out)
+        assert rel(out.cpu().numpy(), ref) <= TOL
+        assert bool((buf[:4 + pad] == 7.0).all()) and bool((buf[4 + pad + 2 * G.n_rows:] == 7.0).all())
+
+
 @pytest.mark.parametrize("name", ["one_wave_ragged", "one_wave_7_columns", "two_rows_8_columns", "one_column",
                                   "four_waves", "empty_cells", "half_steps", "half_steps_odd_rows"])
 def test_ridge_by_shares_of_the_cell_rows_matches_oracle(gpu_lib, name):
