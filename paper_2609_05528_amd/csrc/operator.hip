@@ -2645,8 +2645,12 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     // More than 128 hats: the lean products; records in data-row order where rows share lines with their
     // neighbours (200^2 x 150 frames, 64 vectors: 310 against 365 us; 360^2 x 300, 8 vectors: 285 against
     // 347; 256^2 x 192, whole lines: 168 against 157) or steps are half hats, unless the coefficient
-    // blocks outgrow the last cache (512^2 x 512, 4 vectors: 271 against 297 us; 16: 1418 against 1205).
-    const bool rows = m.Q == 2 ? 4 * m.n_cols * nvec <= ((int64_t)128 << 20) : F % 32 != 0;
+    // blocks outgrow the last cache (512^2 x 512, 4 vectors: 271 against 297 us; 16: 1418 against 1205).  A short
+    // data vector is written by cells soon enough for the parts of a line to meet (122^2, one order, 6 to 8 MB
+    // a vector: 142 frames, 67 vectors 109 us by cells against 125, 190 frames, 8 vectors 24 against 26; 164^2
+    // x 129 frames, 10 MB: 24 against 20).
+    const bool rows = m.Q == 2 ? 4 * m.n_cols * nvec <= ((int64_t)128 << 20)
+                               : F % 32 != 0 && 4 * m.n_rows > ((int64_t)9 << 20);
     return rows ? 13 : 4;
 }
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
@@ -2656,12 +2660,21 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     // Several geometries: the row sweep, which has a form for all members in one launch (12 geometries of
     // 2 to 12 rays a cell: 60 vectors 2.15 ms against 2.54 ms for base cells member by member; 8 vectors 460
     // against 394 us; one vector without row pairs 170 against 227 us with them).
-    if (g->members.size() > 1) return nvec >= 4 ? 19 : 16;
+    // Row pairs need enough waves (pairs, segments of 16 columns, two vectors): 5 members, 4 vectors 417 us against
+    // 317 with single rows and one vector per wave, 7 vectors 541 against 463, 12 members, 4 vectors 580 against 570.
+    if (g->members.size() > 1) {
+        int64_t waves = 0;
+        for (const Member& o : g->members) waves += (int64_t)((o.grid.n_r + 1) / 2) * ((o.grid.n_phi + 15) / 16) * ((nvec + 1) / 2);
+        return waves >= 4096 ? 19 : 16;
+    }
     // One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
     // 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
     // 240 against 248), which need even, aligned rows at half steps.
     const int64_t cells = (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
     if (2 * m.n_rays >= 9 * cells && (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m)) return 23;
+    // Odd rows at half steps have no aligned frame pairs: one vector per wave (89 frames, 12 vectors: 50 us
+    // against 55 with two and 82 with four; 107 frames, 161 vectors: 242, 259, 267).
+    if (m.Q == 2 && m.grid.n_frames % 2) return 16;
     // the row sweep: row pairs (which fall back to single rows for few tasks), or four vectors per wave
     // for middle blocks on grids of many rows (64 x 64 cells, 16 vectors: 34 against 43 us)
     return nvec >= 8 && nvec < 32 && m.grid.n_r >= 64 ? 18 : nvec > 1 ? 19 : 16;
