@@ -33,6 +33,9 @@
  *    been launched and last_error() holds a message for the calling thread.
  *    No C++ exception crosses this boundary.
  *  - The ratio dt_obs/dt_src must be a rational P/Q with Q <= 64, P <= 4096.
+ *  - Scratch that a driver allocates comes from a pool of idle device blocks
+ *    (at most 8 GiB idle per GPU), which go back to the device when an
+ *    allocation fails and when the last geometry handle is freed.
  */
 #ifndef RTT_H
 #define RTT_H
