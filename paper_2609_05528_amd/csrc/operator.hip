@@ -2648,9 +2648,10 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     // blocks outgrow the last cache (512^2 x 512, 4 vectors: 271 against 297 us; 16: 1418 against 1205).  A short
     // data vector is written by cells soon enough for the parts of a line to meet (122^2, one order, 6 to 8 MB
     // a vector: 142 frames, 67 vectors 109 us by cells against 125, 190 frames, 8 vectors 24 against 26; 164^2
-    // x 129 frames, 10 MB: 24 against 20).
+    // x 129 frames, 10 MB: 24 against 20).  Rows of whole 32-byte sectors go by cells up to 256 frames (318^2, one
+    // order, 8 vectors: 176 frames 96 against 115 us, 208 154 against 167, 240 172 against 175; 304 233 against 206).
     const bool rows = m.Q == 2 ? 4 * m.n_cols * nvec <= ((int64_t)128 << 20)
-                               : F % 32 != 0 && 4 * m.n_rows > ((int64_t)9 << 20);
+                               : F % 8 != 0 ? 4 * m.n_rows > ((int64_t)9 << 20) : F % 32 != 0 && F > 256;
     return rows ? 13 : 4;
 }
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
