@@ -1858,7 +1858,7 @@ __device__ __forceinline__ void visit_body(const VisitArgs& a, const float* __re
         // the batch's visit records, scalar loads (the last batch re-reads its last record for
         // the missing ones, which are then switched off)
         // RR = 1: (row, k0, th0, wa | wb, col, order, -); RR = 2: (row, k0, th0,
-        // col | order << 16 | wa0, wb0, wa1, wb1)
+        // col | order << 16 | rows it feeds << 24 | wa0, wb0, wa1, wb1)
         i4v r0[NB], r1[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
@@ -1867,7 +1867,7 @@ __device__ __forceinline__ void visit_body(const VisitArgs& a, const float* __re
             r1[j] = q[1];
         }
         float yv[NB][NVW][V][T], tw[NB][T], wa[NB][RR], wb[NB][RR];
-        int vcol[NB];
+        int vcol[NB], rows_fed[NB];
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const bool valid = e0 + j < vend;
@@ -1885,7 +1885,8 @@ __device__ __forceinline__ void visit_body(const VisitArgs& a, const float* __re
                 const int co = r0[j].w;
                 const int e0b = r1[j].x, e1b = r1[j].y, e2b = r1[j].z, e3b = r1[j].w;
                 col_j = co & 0xFFFF;
-                order = co >> 16;
+                order = (co >> 16) & 0xFF;
+                rows_fed[j] = co >> 24;
                 wa[j][0] = __builtin_bit_cast(float, e0b);
                 wb[j][0] = __builtin_bit_cast(float, e1b);
                 wa[j][1] = __builtin_bit_cast(float, e2b);
@@ -2024,19 +2025,27 @@ __device__ __forceinline__ void visit_body(const VisitArgs& a, const float* __re
                     }
                 }
             }
+            float h[NVW][V];
 #pragma unroll
             for (int u = 0; u < NVW; ++u)
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    float h = 0.f;
+                    h[u][v] = 0.f;
 #pragma unroll
-                    for (int t = 0; t < T; ++t) h += tw[j][t] * yv[j][u][v][t];
-#pragma unroll
-                    for (int r = 0; r < RR; ++r) {
-                        acc_a[r][u][v] += wa[j][r] * h;
-                        acc_b[r][u][v] += wb[j][r] * h;
-                    }
+                    for (int t = 0; t < T; ++t) h[u][v] += tw[j][t] * yv[j][u][v][t];
                 }
+#pragma unroll
+            for (int r = 0; r < RR; ++r) {
+                // (uniform) a row of the pair that the ray does not feed takes nothing, not 0 times its samples
+                if (RR == 2 && BR == 0 && !((rows_fed[j] >> r) & 1)) continue;
+#pragma unroll
+                for (int u = 0; u < NVW; ++u)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        acc_a[r][u][v] += wa[j][r] * h[u][v];
+                        acc_b[r][u][v] += wb[j][r] * h[u][v];
+                    }
+            }
         }
     }
     while (col < ncol) emit();

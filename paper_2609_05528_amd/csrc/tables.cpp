@@ -268,7 +268,8 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
         }
         // set 2: the same sweep for a pair of rows (2p, 2p+1): a ray with base row ib feeds rows ib
         // (1 - fr) and ib + 1 (fr); within a column the order is by base row, so each row sums its
-        // rays in the order of the single-row lists
+        // rays in the order of the single-row lists.  Bits 24 and 25 of col_order: the ray feeds row 2p,
+        // row 2p+1 (a zero weight alone does not say so, and 0 times a non-finite sample is NaN)
         {
             const int vseg = VISIT_SEG_MAX;
             const int nseg = (g.n_phi + vseg - 1) / vseg;
@@ -300,7 +301,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
                                 h.row = rr.row;
                                 h.k0 = rr.k0;
                                 h.th0 = rr.th0;
-                                h.col_order = c | (rr.order << 16);
+                                h.col_order = c | (rr.order << 16) | ((part == 0 ? 1 : part == 1 ? 3 : 2) << 24);
                                 Visit raw;
                                 std::memcpy(&raw, &h, sizeof h);
                                 std::memcpy((char*)&raw + sizeof h, wts, sizeof wts);

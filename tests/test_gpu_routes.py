@@ -1,0 +1,48 @@
+"""Calls at the sizes where the choice of kernels of an unpinned handle turns: a vector alone and inside a
+block, one launch and one launch per geometry, aligned and unaligned data, finite and not.
+
+Equal means equal bits (the same additions in the same order); the oracle checks use the tolerance of the
+other operator tests.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_operator import TOL, rel, say, to_dev
+from tinygeo import tiny_geometry
+
+pytestmark = pytest.mark.gpu
+
+
+def hats(geo, n):
+    geo.grid = dataclasses.replace(geo.grid, n_hat=n)
+    return geo
+
+
+def same(a, b):
+    import torch
+    return bool(torch.equal(torch.isnan(a), torch.isnan(b))) and bool(torch.equal(torch.nan_to_num(a, nan=0.5), torch.nan_to_num(b, nan=0.5)))
+
+
+@pytest.mark.parametrize("dt_obs", [4.0, 2.0])
+def test_non_finite_sample_reaches_the_same_nodes_alone_and_in_a_block(gpu_lib, dt_obs):
+    """150 vectors on 64 x 64 cells take row pairs, a few take single rows, 12 geometries take either in one
+    launch; 16 x 12 cells take the base cells."""
+    import torch
+    rtt = gpu_lib
+    sparse = tiny_geometry(seed=301, rays=(4000, 300, 200), n_r=64, n_phi=64, n_frames=32, dt_obs=dt_obs)
+    dense = tiny_geometry(seed=302, rays=(4000, 300, 200), n_r=12, n_phi=16, n_frames=32, dt_obs=dt_obs)
+    for name, geos in (("pairs", sparse), ("cells", dense), ("batch", [sparse] * 4 + [dense] * 2)):
+        G = rtt.Geometry(geos)
+        for bad in (float("nan"), float("inf"), -float("inf")):
+            say("case non-finite", name, dt_obs, bad)
+            Y, X = torch.randn((150, G.n_rows), device="cuda"), torch.rand((150, G.n_cols), device="cuda")
+            Y[:, 1000 * 32 + 7] = bad
+            X[:, G.n_cols // 2 + 3] = bad
+            y, x = rtt.op_apply(G, X), rtt.op_apply_adjoint(G, Y)
+            assert 0 < int((~torch.isfinite(x[0])).sum()) <= 4 * 3   # four corners, at most three hats
+            for nv in (1, 2, 9):
+                assert same(rtt.op_apply_adjoint(G, Y[:nv].contiguous()), x[:nv]), (name, bad, nv)
+                assert same(rtt.op_apply(G, X[:nv].contiguous()), y[:nv]), (name, bad, nv)
