@@ -158,7 +158,7 @@ __global__ __launch_bounds__(W * WAVE, 4) void k_adjoint_cells(CellArgs a)
             for (int u = 0; u < NVW; ++u) {
                 const __amdgpu_buffer_rsrc_t ry =
                     __builtin_amdgcn_make_buffer_rsrc((void*)(ybase[u] + roff[j]), (short)0, (int)range[j], 0x00020000);
-                // the frame (Q = 1) or the aligned frame pair (Q = 2, even rows: inside the row or outside)
+                // the frame (Q = 1) or the frame pair (Q = 2, even rows: inside the row or outside)
                 // of a hat; frames outside [0, F) read 0 (an earlier frame's offset wraps past the range)
                 auto ld = [&](int off) -> f2 {
                     if constexpr (Q == 1)

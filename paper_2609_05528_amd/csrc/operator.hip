@@ -2663,6 +2663,10 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
                                : F % 8 != 0 ? 4 * m.n_rows > ((int64_t)9 << 20) : F % 32 != 0 && F > 256;
     return rows ? 13 : 4;
 }
+// the base-cell kernel reads these rows: whole frame pairs at Q = 2, at any 4-byte alignment (8-byte buffer
+// loads need no more), so that a block gives the same bits wherever it starts
+static bool cells_rows_ok(const Member& m) { return (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m); }
+
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
 {
     if (m.adj_variant >= 0) return m.adj_variant;
@@ -2679,9 +2683,9 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     }
     // One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
     // 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
-    // 240 against 248), which need even, aligned rows at half steps.
+    // 240 against 248), which need even rows at half steps.
     const int64_t cells = (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
-    if (2 * m.n_rays >= 9 * cells && (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m)) return 23;
+    if (2 * m.n_rays >= 9 * cells && cells_rows_ok(m)) return 23;
     // Odd rows at half steps have no aligned frame pairs: one vector per wave (89 frames, 12 vectors: 50 us
     // against 55 with two and 82 with four; 107 frames, 161 vectors: 242, 259, 267).
     if (m.Q == 2 && m.grid.n_frames % 2) return 16;
@@ -3498,13 +3502,6 @@ static void rows_dispatch(const RowsArgs& a, int nvec, hipStream_t s)
     }
 }
 
-// the base-cell kernel reads these rows: aligned frame pairs at Q = 2
-static bool cells_rows_ok(const Member& m, const float* y, int nvec, int64_t y_stride)
-{
-    const bool fpair = m.Q == 1 || ((m.grid.n_frames % 2) == 0 && (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (y_stride % 2) == 0));
-    return fpair && adjoint_cells_ok(m);
-}
-
 int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec,
                    int64_t y_stride, int64_t x_stride, uint32_t mask, hipStream_t s, int variant)
 {
@@ -3564,7 +3561,7 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
     }
     // base cells: frame pairs at Q = 2; else the single-row lane-shifted form
     if (variant == 23) {
-        if (cells_rows_ok(m, y, nvec, y_stride)) return launch_adjoint_cells(g, m, y, x, nvec, y_stride, x_stride, mask, s);
+        if (cells_rows_ok(m)) return launch_adjoint_cells(g, m, y, x, nvec, y_stride, x_stride, mask, s);
         variant = nvec >= 2 ? 17 : 16;
     }
     if ((variant == 11 || variant >= 14) && !visit_fits(m.n_rows, m.n_cols, y_stride, x_stride, 1)) variant = 2;
@@ -3704,7 +3701,7 @@ bool adjoint_parts(const rtt_geometry* g, const float* y, float* x, float* x2, i
 {
     if (g->members.size() != 1 || nvec == 0) return false;
     const Member& m = g->members[0];
-    if (adjoint_variant_for(g, m, nvec) != 23 || !adjoint_variant_ok(m, 23) || !cells_rows_ok(m, y, nvec, g->n_rows)) return false;
+    if (adjoint_variant_for(g, m, nvec) != 23 || !adjoint_variant_ok(m, 23) || !cells_rows_ok(m)) return false;
     *rc = launch_adjoint_cells(g, m, y, x, nvec, g->n_rows, g->n_cols, effective_mask(m, mask), s, x2);
     return true;
 }

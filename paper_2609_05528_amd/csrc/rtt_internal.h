@@ -148,7 +148,7 @@ int launch_apply(const rtt_geometry* g, const Member& m, const float* x, float* 
                  int64_t x_stride, int64_t y_stride, uint32_t mask, hipStream_t s, int variant);
 int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec,
                    int64_t y_stride, int64_t x_stride, uint32_t mask, hipStream_t s, int variant);
-// A^T over base cells (adjoint_cells.hip); data rows must be even and 8-byte aligned when Q = 2
+// A^T over base cells (adjoint_cells.hip); data rows must be even when Q = 2
 bool adjoint_cells_ok(const Member& m);
 int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec, int64_t y_stride,
                          int64_t x_stride, uint32_t mask, hipStream_t s, float* x2 = nullptr);

@@ -46,3 +46,23 @@ def test_non_finite_sample_reaches_the_same_nodes_alone_and_in_a_block(gpu_lib, 
             for nv in (1, 2, 9):
                 assert same(rtt.op_apply_adjoint(G, Y[:nv].contiguous()), x[:nv]), (name, bad, nv)
                 assert same(rtt.op_apply(G, X[:nv].contiguous()), y[:nv]), (name, bad, nv)
+
+
+@pytest.mark.parametrize("rays", [(300, 40), (900, 90), (4000, 400)])
+@pytest.mark.parametrize("frames", [60, 256])
+def test_half_step_adjoint_gives_the_same_bits_at_any_alignment(gpu_lib, rays, frames):
+    import torch
+    rtt = gpu_lib
+    geo = tiny_geometry(seed=303, rays=rays, n_r=6, n_phi=9, n_frames=frames, dt_obs=2.0)
+    G = rtt.Geometry(geo)
+    say("case alignment", rays, frames, rtt.variant_names(True)[G.members[0]["adjoint_variant"]])
+    Y = to_dev(np.random.default_rng(7).standard_normal((5, G.n_rows)))
+    x = rtt.op_apply_adjoint(G, Y)
+    assert rel(x.cpu().numpy(), oracle.adjoint(geo, Y.double().cpu().numpy())) <= TOL
+    buf = torch.full((5 * G.n_rows + 8,), float("nan"), device="cuda")
+    for pad in (1, 2, 3):
+        off = buf[pad:pad + 5 * G.n_rows].view(5, G.n_rows)
+        off.copy_(Y)
+        assert torch.equal(rtt.op_apply_adjoint(G, off), x), pad
+        assert torch.equal(rtt.op_apply_adjoint(G, off[:1]), x[:1]), pad
+        buf.fill_(float("nan"))
