@@ -689,7 +689,8 @@ __device__ __forceinline__ FwdRec load_const_rec(const FwdRec* p)
 // of ZS floats starting at zs0, hat h of ray j at zs0[j*ZS + h]) are interpolated to the frames
 // [f0, fend) of each ray and written to its data row.  With aligned rows (VEC4): Q = 1 takes one
 // ray per pass with two frames per lane (8-byte stores), Q = 2 four frames per lane (16-byte
-// stores); otherwise one frame per lane.
+// stores); otherwise one frame per lane.  Every product and sum of the lean and absolute-hat forms is
+// written as the fused operation it is, so that all of them give the same bits.
 // Hats staged per ray chunk (LDS row length) and the longest frame chunk they serve: a chunk
 // of fc frames starting at hat klo reads hats klo .. klo + fc/Q + 1.
 constexpr int LEAN_ZI = 3;
@@ -726,10 +727,10 @@ __device__ __forceinline__ void lean_emit(const float* zs0, const float* th0, co
                     const f4 za = *(const f4*)zr;
                     const float z4 = zr[4];
                     f4 v;
-                    v[0] = za[0] + th * (za[1] - za[0]);
-                    v[1] = za[1] + th * (za[2] - za[1]);
-                    v[2] = za[2] + th * (za[3] - za[2]);
-                    v[3] = za[3] + th * (z4 - za[3]);
+                    v[0] = fmaf(th, za[1] - za[0], za[0]);
+                    v[1] = fmaf(th, za[2] - za[1], za[1]);
+                    v[2] = fmaf(th, za[3] - za[2], za[2]);
+                    v[3] = fmaf(th, z4 - za[3], za[3]);
                     __builtin_nontemporal_store(v, (f4*)(yr + f0 + q));
                 }
             }
@@ -752,8 +753,8 @@ __device__ __forceinline__ void lean_emit(const float* zs0, const float* th0, co
                 const f2 za = *(const f2*)zr;
                 const float zc = zr[2];
                 f2 v;
-                v[0] = za[0] + th * (za[1] - za[0]);
-                v[1] = za[1] + th * (zc - za[1]);
+                v[0] = fmaf(th, za[1] - za[0], za[0]);
+                v[1] = fmaf(th, zc - za[1], za[1]);
                 if (q < nf) __builtin_nontemporal_store(v, (f2*)(yr + f0 + q));
             }
         }
@@ -778,10 +779,10 @@ __device__ __forceinline__ void lean_emit(const float* zs0, const float* th0, co
                 const float a1 = c1 ? z1 : z0, b1 = c1 ? z2 : z1;
                 const float a3 = c1 ? z2 : z1, b3 = c1 ? z3 : z2;
                 f4 v;
-                v[0] = z0 + th * (z1 - z0);
-                v[1] = a1 + th1 * (b1 - a1);
-                v[2] = z1 + th * (z2 - z1);
-                v[3] = a3 + th1 * (b3 - a3);
+                v[0] = fmaf(th, z1 - z0, z0);
+                v[1] = fmaf(th1, b1 - a1, a1);
+                v[2] = fmaf(th, z2 - z1, z1);
+                v[3] = fmaf(th1, b3 - a3, a3);
                 if (4 * g < nf) __builtin_nontemporal_store(v, (f4*)(yr + f0 + 4 * g));
             }
         }
@@ -807,7 +808,7 @@ __device__ __forceinline__ void lean_emit(const float* zs0, const float* th0, co
                     th = odd ? (c1 ? th0[j] - 0.5f : th0[j] + 0.5f) : th0[j];
                 }
                 const float za = zs[j][jz], zb = zs[j][jz + 1];
-                __builtin_nontemporal_store(za + th * (zb - za), yr + f0 + q);
+                __builtin_nontemporal_store(fmaf(th, zb - za, za), yr + f0 + q);
             }
         }
     }
@@ -881,7 +882,7 @@ __device__ __forceinline__ void lean_emit_staged(const float* zs0, const float* 
             const int q = lane + t * WAVE;
             if (q >= F) break;
             const float za = zs[j][q], zb = zs[j][q + 1];
-            ob[pad + j * F + q] = za + th * (zb - za);
+            ob[pad + j * F + q] = fmaf(th, zb - za, za);
         }
     }
     range_store<NB>(ob, pad, NB * F, yb);
@@ -969,8 +970,9 @@ __device__ __forceinline__ void lean_body(const LeanArgs& a, const float* __rest
 #pragma unroll
         for (int it = 0; it < ZI; ++it) {
             // lanes of hats outside [0, K) loaded zeros; rays that are off are not written
-            const float z = live[j][it] ? rc[j].b00 * xv[j][it][0] + rc[j].b10 * xv[j][it][1] +
-                                              rc[j].b01 * xv[j][it][2] + rc[j].b11 * xv[j][it][3]
+            const float z = live[j][it] ? fmaf(rc[j].b11, xv[j][it][3],
+                                               fmaf(rc[j].b01, xv[j][it][2],
+                                                    fmaf(rc[j].b10, xv[j][it][1], rc[j].b00 * xv[j][it][0])))
                                         : 0.f;
             zs[j][lane + it * WAVE] = z;
         }
@@ -1056,7 +1058,10 @@ __device__ __forceinline__ void leanq_body(const LeanArgs& a, const float* __res
         row[j] = rc[j].row;
         const int klo = rc[j].k0 + f0 / Q;
         const int base = 4 * lane - (klo - (klo & ~3));   // LDS position of the quad's first hat
-        const f4 z = rc[j].b00 * xq[j][0] + rc[j].b10 * xq[j][1] + rc[j].b01 * xq[j][2] + rc[j].b11 * xq[j][3];
+        f4 z;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            z[t] = fmaf(rc[j].b11, xq[j][3][t], fmaf(rc[j].b01, xq[j][2][t], fmaf(rc[j].b10, xq[j][1][t], rc[j].b00 * xq[j][0][t])));
         // every position of z[j][0 .. W) is written by exactly one lane
         if (lane < NQ) {
 #pragma unroll
@@ -1093,7 +1098,7 @@ __global__ __launch_bounds__(A_WAVES * WAVE) void k_apply_lean(LeanArgs a)
 // records are sorted by base cell) share one set of gathers.  Each ray's combined series over
 // all K hats goes to an LDS row and its whole frame range is written from it (no frame chunks);
 // hats outside [0, K) read as 0.  The products and the order of the sums are those of the lean
-// form (the two agree to rounding: FMA contraction may differ).
+// form, bit for bit.
 // --------------------------------------------------------------------------------------------
 constexpr int ABS_KMAX = 2 * WAVE;
 
@@ -1128,8 +1133,6 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
         const int64_t ri = r0 + j;
         rc[j] = load_const_rec(a.rec + __builtin_amdgcn_readfirstlane((int)(ri < a.n_rays ? ri : r0)));
     }
-    // every product and sum is written as the fused operation it is, so that each form (wide or narrow
-    // stores, staged rows, one launch for many members) gives the same bits
     float xv[NB][2][4];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {

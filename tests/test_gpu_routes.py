@@ -66,3 +66,32 @@ def test_half_step_adjoint_gives_the_same_bits_at_any_alignment(gpu_lib, rays, f
         assert torch.equal(rtt.op_apply_adjoint(G, off), x), pad
         assert torch.equal(rtt.op_apply_adjoint(G, off[:1]), x[:1]), pad
         buf.fill_(float("nan"))
+
+
+@pytest.mark.parametrize("dt_obs", [4.0, 2.0])
+@pytest.mark.parametrize("n_hat,frames,rays", [(128, (96, 97, 134), 900), (170, (150, 192, 301), 900), (200, (134, 192, 150), 12000)])
+def test_forward_gives_the_same_bits_by_every_lean_route(gpu_lib, dt_obs, n_hat, frames, rays):
+    """The variants that an unpinned handle chooses from, alone and in one launch, at any start of the block."""
+    import torch
+    rtt = gpu_lib
+    geos = [hats(tiny_geometry(seed=305 + i, rays=(rays, rays // 8, 80), n_r=6, n_phi=9, n_frames=f, dt_obs=dt_obs), n_hat)
+            for i, f in enumerate(frames)]
+    G = rtt.Geometry(geos)
+    X = to_dev(np.random.default_rng(8).random((5, G.n_cols)))
+    y = rtt.op_apply(G, X)
+    for geo, m in zip(geos, G.members):
+        cs, rs = slice(m["col_offset"], m["col_offset"] + m["n_cols"]), slice(m["row_offset"], m["row_offset"] + m["n_rows"])
+        assert rel(y[0, rs].cpu().numpy(), oracle.forward(geo, X[0, cs].double().cpu().numpy())) <= TOL
+    buf = torch.empty((5 * G.n_rows + 8,), device="cuda")
+    names = ["lean4", "lean8", "lean4r"] + (["lean4q"] if n_hat % 4 == 0 else []) + (["abs4", "abs8", "abs4r"] if n_hat <= 128 else [])
+    for name in [None] + names:
+        if name:
+            G.set_variant(apply=rtt.variant_names(False).index(name))
+        for mode in (0, 1, 2):
+            G.set_batch_mode(mode, mode)
+            for pad in (0, 1, 2):
+                say("case forward bits", dt_obs, n_hat, name, mode, pad)
+                for nv in (1, 5):
+                    out = buf[pad:pad + nv * G.n_rows].view(nv, G.n_rows)
+                    rtt.op_apply(G, X[:nv], y=out)
+                    assert torch.equal(out, y[:nv]), (name, mode, pad, nv)
