@@ -2674,16 +2674,10 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
 {
     if (m.adj_variant >= 0) return m.adj_variant;
     if (!visit_supported(m)) return 2;
-    // Several geometries: the row sweep, which has a form for all members in one launch (12 geometries of
-    // 2 to 12 rays a cell: 60 vectors 2.15 ms against 2.54 ms for base cells member by member; 8 vectors 460
-    // against 394 us; one vector without row pairs 170 against 227 us with them).
-    // Row pairs need enough waves (pairs, segments of 16 columns, two vectors): 5 members, 4 vectors 417 us against
-    // 317 with single rows and one vector per wave, 7 vectors 541 against 463, 12 members, 4 vectors 580 against 570.
-    if (g->members.size() > 1) {
-        int64_t waves = 0;
-        for (const Member& o : g->members) waves += (int64_t)((o.grid.n_r + 1) / 2) * ((o.grid.n_phi + 15) / 16) * ((nvec + 1) / 2);
-        return waves >= 4096 ? 19 : 16;
-    }
+    // Several geometries: the row sweep (12 geometries of 2 to 12 rays a cell: 60 vectors 2.15 ms against
+    // 2.54 ms for base cells member by member; 8 vectors 460 against 394 us; one vector without row pairs
+    // 170 against 227 us with them).  For one launch of several of them see adjoint_group.
+    if (g->members.size() > 1) return g->pair_tasks * ((nvec + 1) / 2) >= 4096 ? 19 : 16;
     // One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
     // 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
     // 240 against 248), which need even rows at half steps.
@@ -2695,6 +2689,24 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     // the row sweep: row pairs (which fall back to single rows for few tasks), or four vectors per wave
     // for middle blocks on grids of many rows (64 x 64 cells, 16 vectors: 34 against 43 us)
     return nvec >= 8 && nvec < 32 && m.grid.n_r >= 64 ? 18 : nvec > 1 ? 19 : 16;
+}
+
+// The adjoint variant of the unpinned members among [b, e) when they go in one launch.  Row pairs need enough
+// waves in it (pairs, segments of 16 columns, two vectors): 5 members of up to 4.3 rays a cell, 7 vectors, 2560
+// waves 107 us against 91 with single rows and one vector per wave, 12 vectors, 3840 waves 140 against 161; 12
+// members of up to 12 rays a cell, 4 vectors, 3072 waves 345 against 333, 6 vectors, 4608 waves 394 against 417.
+// Members of fewer than 4 rays a cell have shorter waves (16 members of 32 x 32 cells, 3.7 rays a cell: 1024 waves
+// 68 us against 56, 2048 75 against 98; of 16 x 16 cells, 1.5 rays a cell: 24 against 27, 31 against 47).
+static int adjoint_group(const rtt_geometry* g, int b, int e, int nvec)
+{
+    int64_t tasks = 0;
+    bool few = true;
+    for (int i = b; i < e; ++i) {
+        const Member& m = g->members[i];
+        tasks += m.pair_tasks;
+        few = few && m.n_rays < 4 * (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
+    }
+    return tasks * ((nvec + 1) / 2) >= (few ? 2048 : 4096) ? 19 : 16;
 }
 
 template <int TP, int TQ, int NB, int ZI>
@@ -3416,12 +3428,13 @@ static bool adjoint_multi(const rtt_geometry* g, int b, int e, const float* y, f
                           hipStream_t s, bool persist, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
-    const int v0 = adjoint_variant_for(g, m0, nvec);
+    const int vu = adjoint_group(g, b, e, nvec);   // unpinned members
+    const int v0 = m0.adj_variant >= 0 ? m0.adj_variant : vu;
     bool pair = (((uintptr_t)y) & 7) == 0 && (nvec == 1 || (g->n_rows % 2) == 0);
     int64_t wide = 0;
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
-        if (!visit_supported(m) || m.Q != m0.Q || adjoint_variant_for(g, m, nvec) != v0 ||
+        if (!visit_supported(m) || m.Q != m0.Q || (m.adj_variant >= 0 ? m.adj_variant : vu) != v0 ||
             (v0 != 11 && v0 != 16 && v0 != 19 && v0 != 20))
             return false;
         pair = pair && (m.grid.n_frames % 2) == 0 && (m.row_offset % 2) == 0;
@@ -3707,6 +3720,17 @@ bool adjoint_parts(const rtt_geometry* g, const float* y, float* x, float* x2, i
     if (adjoint_variant_for(g, m, nvec) != 23 || !adjoint_variant_ok(m, 23) || !cells_rows_ok(m)) return false;
     *rc = launch_adjoint_cells(g, m, y, x, nvec, g->n_rows, g->n_cols, effective_mask(m, mask), s, x2);
     return true;
+}
+
+int adjoint_variant_of_call(const rtt_geometry* g, int i, int nvec)
+{
+    const Member& m = g->members[i];
+    const int b = i / MULTI_MAX * MULTI_MAX, e = std::min((int)g->members.size(), b + MULTI_MAX);
+    int rc = RTT_OK;
+    if (m.adj_variant < 0 && g->members.size() > 1 && g->batch_adjoint_mode != 0 &&
+        adjoint_multi(g, b, e, nullptr, nullptr, nvec, 0u, nullptr, false, &rc, true))
+        return adjoint_group(g, b, e, nvec);
+    return adjoint_variant_for(g, m, nvec);
 }
 
 int whole_operator_launches(const rtt_geometry* g, bool adjoint)

@@ -81,6 +81,7 @@ struct Member {
     int64_t rays_per_order[8];
     int32_t adj_variant;   // pinned adjoint kernel variant (set or tuned); -1: chosen for each call
     int32_t apply_variant; // pinned forward kernel variant, or -1
+    int64_t pair_tasks;    // row pairs x 16-column segments (tasks of visit set 2)
     uint64_t digest;       // FNV-1a of the grid and this member's device records
     // visit-list sets: [0] single rows, 16-column segments (many vectors per call); [1] single
     // rows, narrower segments chosen so one vector alone gives enough (row, segment) tasks;
@@ -116,6 +117,7 @@ struct rtt_geometry {
     // grow-only scratch of the stream-ordered (graph-capturable) solver mode, kept across calls
     mutable rtt::Workspace* solve_ws = nullptr;
     int64_t n_rows = 0, n_cols = 0, n_rays = 0;
+    int64_t pair_tasks = 0;             // sum over the members
     int64_t table_bytes = 0;
     // whole-operator calls on G > 1 members: 0 = one launch per member, 1 = one launch for
     // up to 16 members, 2 = the same as a persistent launch (one block per resident slot)
@@ -156,9 +158,11 @@ int n_adjoint_variants();
 int n_apply_variants();
 const char* adjoint_variant_name(int v);
 const char* apply_variant_name(int v);
-// the variant a call on nvec vectors uses: the pinned one, or the one its sizes choose
+// the variant of a member launched by itself on nvec vectors: the pinned one, or the one its sizes choose
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec);
 int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec);
+// the variant that member i has in a whole-operator call on nvec vectors
+int adjoint_variant_of_call(const rtt_geometry* g, int i, int nvec);
 bool visit_supported(const Member& m);
 bool lean_supported(const Member& m);
 // forward / adjoint variant v can run on member m (ratio and size limits)

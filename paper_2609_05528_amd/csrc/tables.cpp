@@ -416,6 +416,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
         row_off += m.n_rows;
         col_off += m.n_cols;
         m.adj_variant = m.apply_variant = -1;
+        m.pair_tasks = (int64_t)((g.n_r + 1) / 2) * m.nseg[2];
         m.digest = fnv1a(&g, sizeof(g));
         m.digest = fnv1a(gr.data(), gr.size() * sizeof(RayRec), m.digest);
     }
@@ -429,6 +430,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
     h->n_rows = row_off;
     h->n_cols = col_off;
     h->n_rays = (int64_t)recs.size();
+    for (const Member& m : h->members) h->pair_tasks += m.pair_tasks;
     hipGetDevice(&h->device);
     size_t rb = recs.size() * sizeof(RayRec), cb = cstart.size() * sizeof(int32_t);
     size_t vb = std::max<size_t>(visits.size(), 1) * sizeof(Visit), tb = vtask.size() * sizeof(int64_t);
@@ -515,7 +517,7 @@ extern "C" int geometry_member(const rtt_geometry* g, int32_t idx, rtt_member_in
     info->n_cols = m.n_cols;
     for (int n = 0; n < 8; ++n) info->rays_per_order[n] = m.rays_per_order[n];
     info->apply_variant = apply_variant_for(g, m, 1);
-    info->adjoint_variant = adjoint_variant_for(g, m, 1);
+    info->adjoint_variant = adjoint_variant_of_call(g, idx, 1);
     info->digest = m.digest;
     return RTT_OK;
 }

@@ -95,3 +95,18 @@ def test_forward_gives_the_same_bits_by_every_lean_route(gpu_lib, dt_obs, n_hat,
                     out = buf[pad:pad + nv * G.n_rows].view(nv, G.n_rows)
                     rtt.op_apply(G, X[:nv], y=out)
                     assert torch.equal(out, y[:nv]), (name, mode, pad, nv)
+
+
+def test_host_cost_of_a_call_grows_with_the_members_not_their_square(gpu_lib):
+    """4096 members, the most a handle takes.  Linear host work is well below a millisecond; a pass over all
+    members for each of them was 16."""
+    import time
+    rtt = gpu_lib
+    G = rtt.Geometry([tiny_geometry(seed=306, rays=(6, 3), n_r=4, n_phi=6)] * 4096)
+    best = 1.0
+    for _ in range(5):
+        t0 = time.perf_counter()
+        assert G.launches[1] == 4096 // 16
+        best = min(best, time.perf_counter() - t0)
+    say("case host cost", best)
+    assert best < 3e-3
