@@ -144,7 +144,11 @@ int geometry_set_variant(rtt_geometry* geom, int32_t g, int32_t apply_variant, i
  * that stride over the work).  Modes 1 and 2 apply when every geometry of the
  * group uses one lean, absolute-hat (abs4) or register forward variant and a
  * visit-list adjoint variant, with one common dt_obs/dt_src; otherwise the
- * call falls back to one launch per geometry.
+ * call falls back to one launch per geometry.  Unpinned geometries are given
+ * one variant for the launch.  Until the forward mode is set by this call,
+ * op_apply on unpinned geometries takes one launch for the calls that it makes
+ * faster (geometries that write less than 24 MB each) and one per geometry
+ * for the others.
  * -1 leaves a mode unchanged.  geometry_tune picks the fastest.  All modes give
  * bitwise identical results.  Errors: RTT_EINVAL for other values.
  */

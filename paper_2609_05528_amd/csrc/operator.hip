@@ -2633,8 +2633,8 @@ static int reg_lpr(int64_t F)
     return best;
 }
 
-// The variant of a member that neither geometry_set_variant nor geometry_tune has pinned.  Which
-// arithmetic a handle uses (the lean or the absolute-hat products, the row sweeps or the base cells)
+// The variant of a member launched by itself that neither geometry_set_variant nor geometry_tune has pinned.
+// Which arithmetic a handle uses (row sweeps or base cells; the lean and absolute-hat forms add alike)
 // depends on the geometry alone, never on the number of vectors, so a vector gets the same bits alone and
 // inside a block, and in every launch mode; the forms of one arithmetic are chosen by the call's size.
 int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
@@ -2646,9 +2646,7 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
         // Absolute hats.  Rows that end inside a 128-byte line leave staged and aligned when they are long
         // enough to outweigh the lost gather reuse (60 vectors on 64 x 64 cells: 134, 143 and
         // 151 frames 301, 144 and 396 us row-ordered against 368, 161 and 548; 125 frames 104 against 66, 160
-        // frames, whole lines, 213 against 160).  One launch for all members serves one or two vectors (12
-        // geometries: 59 against 71 us; 8 vectors 438 against 366).
-        if (g->members.size() > 1 && nvec <= 2) return 11;
+        // frames, whole lines, 213 against 160).
         // So do rows of whole lines that a member's place in the data vector moves off them (the sixth of the
         // 12, 160 frames: 214 us row-ordered, 257 by cells; 160 where its lines are whole).
         const bool ragged = F % 32 != 0 || (g->members.size() > 1 && (m.row_offset % 32 != 0 || g->n_rows % 32 != 0));
@@ -2666,6 +2664,35 @@ int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec)
                                : F % 8 != 0 ? 4 * m.n_rows > ((int64_t)9 << 20) : F % 32 != 0 && F > 256;
     return rows ? 13 : 4;
 }
+// Whether the unpinned members among [b, e) go in one launch, and then with which variant.  The records in
+// data-row order only where every member would take them by itself and, at whole steps, the data outgrow the
+// caches in which the parts of a line meet (6 members of 64 x 64 cells, 150 to 156 frames: 91 MB 46 us against 39 by
+// cells, 183 MB 79 against 87; 4 of 128 to 134 frames: 105 MB 54 against 49).  Where the caller asked for one launch,
+// always.  Else while a member writes less than 24 MB on average: a launch of its own costs at least 3 us (16
+// members of 16 x 16 cells, 3 vectors: 9 us in one, 50 in 16), but lets one member's coefficients have the caches
+// to themselves (12 members of 64 x 64 cells, 0.2M to 1.3M frames a vector, 12 x 60 batch: 11 MB a member 54 us in
+// one and 73 apart, 23 MB 102 and 112, 34 MB 147 and 148, 91 MB 396 and 312).  Half of that where some members have
+// more than 128 hats and all would take the lean form for them (12 members of 32 x 32 cells: 10 MB 68 and 69, 14 MB
+// 89 and 86, 20 MB 124 and 105).
+static bool apply_group(const rtt_geometry* g, int b, int e, int nvec, int* variant)
+{
+    int64_t rows = 0;
+    int lean = 0, row_order = 0, abs = 0;
+    for (int i = b; i < e; ++i) {
+        const Member& m = g->members[i];
+        rows += m.n_rows;
+        if (m.apply_variant >= 0) continue;
+        if (!lean_supported(m)) return false;
+        if (m.grid.n_hat <= ABS_KMAX) ++abs;
+        else if (apply_variant_for(g, m, nvec) == 13) ++row_order;
+        else ++lean;
+    }
+    const bool spread = g->members[b].Q == 2 || 4 * rows * nvec > ((int64_t)128 << 20);
+    *variant = lean + row_order == 0 ? 11 : lean + abs == 0 && spread ? 13 : 4;
+    const int64_t line = (int64_t)(abs > 0 && lean + row_order > 0 ? 3 : 6) * 1000000;
+    return g->batch_apply_asked || abs + lean + row_order == 0 || rows * nvec < line * (e - b);
+}
+
 // the base-cell kernel reads these rows: whole frame pairs at Q = 2, at any 4-byte alignment (8-byte buffer
 // loads need no more), so that a block gives the same bits wherever it starts
 static bool cells_rows_ok(const Member& m) { return (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m); }
@@ -2695,8 +2722,9 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
 // waves in it (pairs, segments of 16 columns, two vectors): 5 members of up to 4.3 rays a cell, 7 vectors, 2560
 // waves 107 us against 91 with single rows and one vector per wave, 12 vectors, 3840 waves 140 against 161; 12
 // members of up to 12 rays a cell, 4 vectors, 3072 waves 345 against 333, 6 vectors, 4608 waves 394 against 417.
-// Members of fewer than 4 rays a cell have shorter waves (16 members of 32 x 32 cells, 3.7 rays a cell: 1024 waves
-// 68 us against 56, 2048 75 against 98; of 16 x 16 cells, 1.5 rays a cell: 24 against 27, 31 against 47).
+// Members of fewer than 4 rays a cell and at most 128 hats have shorter waves (16 members of 32 x 32 cells, 3.7
+// rays a cell: 1024 waves 68 us against 56, 2048 75 against 98; of 16 x 16 cells, 1.5 rays a cell: 24 against 27, 31
+// against 47; 3.7 rays a cell and 169 hats: 2048 waves 157 against 130).
 static int adjoint_group(const rtt_geometry* g, int b, int e, int nvec)
 {
     int64_t tasks = 0;
@@ -2704,7 +2732,7 @@ static int adjoint_group(const rtt_geometry* g, int b, int e, int nvec)
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
         tasks += m.pair_tasks;
-        few = few && m.n_rays < 4 * (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
+        few = few && m.grid.n_hat <= 128 && m.n_rays < 4 * (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
     }
     return tasks * ((nvec + 1) / 2) >= (few ? 2048 : 4096) ? 19 : 16;
 }
@@ -3197,11 +3225,11 @@ static bool apply_multi_reg(const rtt_geometry* g, int b, int e, const float* x,
                             hipStream_t s, bool persist, bool shared, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
-    const int v0 = apply_variant_for(g, m0, nvec);
+    const int v0 = m0.apply_variant;   // reg1 or reg2: pinned
     bool vec4 = (((uintptr_t)y) & 15) == 0 && (nvec == 1 || (g->n_rows % 4) == 0);
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
-        if (!lean_supported(m) || m.Q != m0.Q || apply_variant_for(g, m, nvec) != v0) return false;
+        if (!lean_supported(m) || m.Q != m0.Q || m.apply_variant != v0) return false;
         vec4 = vec4 && (m.grid.n_frames % 4) == 0 && (m.row_offset % 4) == 0;
     }
     const int NI = v0 == 6 ? 1 : 2;
@@ -3267,7 +3295,9 @@ static bool apply_multi(const rtt_geometry* g, int b, int e, const float* x, flo
                         hipStream_t s, bool persist, bool shared, int* rc, bool probe = false)
 {
     const Member& m0 = g->members[b];
-    const int v0 = apply_variant_for(g, m0, nvec);
+    int vu = 0;
+    if (!apply_group(g, b, e, nvec, &vu)) return false;
+    const int v0 = m0.apply_variant >= 0 ? m0.apply_variant : vu;
     if (v0 == 6 || v0 == 7)
         return apply_multi_reg(g, b, e, x, y, nvec, mask, s, persist, shared, rc, probe);
     // wide output stores (8-byte aligned rows at Q = 1, 16-byte at Q = 2), decided per member
@@ -3276,8 +3306,7 @@ static bool apply_multi(const rtt_geometry* g, int b, int e, const float* x, flo
     bool all8 = true, use_abs = v0 == 11;
     for (int i = b; i < e; ++i) {
         const Member& m = g->members[i];
-        const int vi = apply_variant_for(g, m, nvec);
-        if (m.apply_variant < 0 && nvec > 2) return false;   // unpinned members: see apply_variant_for
+        const int vi = m.apply_variant >= 0 ? m.apply_variant : vu;
         if (use_abs) {
             if (!apply_variant_ok(m, 11) || m.Q != m0.Q || vi != 11) return false;
             continue;
@@ -3720,6 +3749,17 @@ bool adjoint_parts(const rtt_geometry* g, const float* y, float* x, float* x2, i
     if (adjoint_variant_for(g, m, nvec) != 23 || !adjoint_variant_ok(m, 23) || !cells_rows_ok(m)) return false;
     *rc = launch_adjoint_cells(g, m, y, x, nvec, g->n_rows, g->n_cols, effective_mask(m, mask), s, x2);
     return true;
+}
+
+int apply_variant_of_call(const rtt_geometry* g, int i, int nvec)
+{
+    const Member& m = g->members[i];
+    const int b = i / MULTI_MAX * MULTI_MAX, e = std::min((int)g->members.size(), b + MULTI_MAX);
+    int rc = RTT_OK, vu = 0;
+    if (m.apply_variant < 0 && g->members.size() > 1 && g->batch_apply_mode != 0 && apply_group(g, b, e, nvec, &vu) &&
+        apply_multi(g, b, e, nullptr, nullptr, nvec, 0u, nullptr, false, false, &rc, true))
+        return vu;
+    return apply_variant_for(g, m, nvec);
 }
 
 int adjoint_variant_of_call(const rtt_geometry* g, int i, int nvec)

@@ -122,6 +122,7 @@ struct rtt_geometry {
     // whole-operator calls on G > 1 members: 0 = one launch per member, 1 = one launch for
     // up to 16 members, 2 = the same as a persistent launch (one block per resident slot)
     int32_t batch_apply_mode = 1, batch_adjoint_mode = 1;
+    bool batch_apply_asked = false;     // the forward mode was set by the caller
     int device = 0;
     // per member: delays and |weights| of the order-0 rays with non-zero weight (host copies for the
     // direct throughput age boundary)
@@ -162,6 +163,7 @@ const char* apply_variant_name(int v);
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec);
 int apply_variant_for(const rtt_geometry* g, const Member& m, int nvec);
 // the variant that member i has in a whole-operator call on nvec vectors
+int apply_variant_of_call(const rtt_geometry* g, int i, int nvec);
 int adjoint_variant_of_call(const rtt_geometry* g, int i, int nvec);
 bool visit_supported(const Member& m);
 bool lean_supported(const Member& m);

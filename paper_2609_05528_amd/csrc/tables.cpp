@@ -500,7 +500,10 @@ extern "C" int geometry_set_batch_mode(rtt_geometry* g, int32_t apply_mode, int3
     if (!valid_handle(g)) return fail(RTT_EINVAL, "invalid geometry handle");
     if (apply_mode < -1 || apply_mode > 2 || adjoint_mode < -1 || adjoint_mode > 2)
         return fail(RTT_EINVAL, "launch mode must be -1 (unchanged), 0, 1 or 2");
-    if (apply_mode >= 0) g->batch_apply_mode = apply_mode;
+    if (apply_mode >= 0) {
+        g->batch_apply_mode = apply_mode;
+        g->batch_apply_asked = true;
+    }
     if (adjoint_mode >= 0) g->batch_adjoint_mode = adjoint_mode;
     return RTT_OK;
 }
@@ -516,7 +519,7 @@ extern "C" int geometry_member(const rtt_geometry* g, int32_t idx, rtt_member_in
     info->col_offset = m.col_offset;
     info->n_cols = m.n_cols;
     for (int n = 0; n < 8; ++n) info->rays_per_order[n] = m.rays_per_order[n];
-    info->apply_variant = apply_variant_for(g, m, 1);
+    info->apply_variant = apply_variant_of_call(g, idx, 1);
     info->adjoint_variant = adjoint_variant_of_call(g, idx, 1);
     info->digest = m.digest;
     return RTT_OK;

@@ -110,3 +110,59 @@ def test_host_cost_of_a_call_grows_with_the_members_not_their_square(gpu_lib):
         best = min(best, time.perf_counter() - t0)
     say("case host cost", best)
     assert best < 3e-3
+
+
+def kernel_nodes(fn):
+    """Kernels that one call launches, counted in a captured graph."""
+    import ctypes
+    import torch
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    n = ctypes.c_size_t()
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert hip.hipGraphGetNodes(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def launches_and_bits(rtt, geos, nvecs, default):
+    """Launches of A at every mode against `default` (those of a handle whose mode was never set), the bits of
+    each against the first, and the oracle's values."""
+    import torch
+    G = rtt.Geometry(geos)
+    X = to_dev(np.random.default_rng(9).random((max(nvecs), G.n_cols)))
+    Y = torch.empty((max(nvecs), G.n_rows), device="cuda")
+    y = rtt.op_apply(G, X)
+    for geo, m in zip(geos, G.members):
+        cs, rs = slice(m["col_offset"], m["col_offset"] + m["n_cols"]), slice(m["row_offset"], m["row_offset"] + m["n_rows"])
+        assert rel(y[0, rs].cpu().numpy(), oracle.forward(geo, X[0, cs].double().cpu().numpy())) <= TOL
+    for mode in (None, 0, 1, 2):
+        if mode is not None:
+            G.set_batch_mode(apply=mode)
+        for nv in nvecs:
+            want = default if mode is None else len(geos) if mode == 0 else (len(geos) + 15) // 16
+            n = kernel_nodes(lambda: rtt.op_apply(G, X[:nv], y=Y[:nv]))
+            say("case launches", len(geos), mode, nv, n)
+            assert n == want, (mode, nv)
+            assert torch.equal(Y[:nv], y[:nv]), (mode, nv)
+
+
+def test_small_geometries_go_in_one_launch_at_any_number_of_vectors(gpu_lib):
+    geos = [tiny_geometry(seed=310 + i, rays=(90 + 30 * i, 12, 8), n_r=6, n_phi=9, n_frames=32 + 3 * i) for i in range(3)]
+    launches_and_bits(gpu_lib, [geos[i % 3] for i in range(18)], (1, 2, 3, 9), 2)
+
+
+@pytest.mark.parametrize("dt_obs", [4.0, 2.0])
+def test_geometries_of_few_and_of_many_hats_share_a_launch(gpu_lib, dt_obs):
+    geos = [hats(tiny_geometry(seed=313 + i, rays=(90, 12, 8), n_r=6, n_phi=9, n_frames=f, dt_obs=dt_obs), n)
+            for i, (f, n) in enumerate(((40, 60), (151, 170), (134, 128), (192, 129)))]
+    launches_and_bits(gpu_lib, geos, (1, 3), 1)
+
+
+def test_a_launch_mode_that_was_set_holds_for_large_geometries(gpu_lib):
+    """8 vectors of about 8 MB a geometry go by one launch a geometry unless the caller asked for one."""
+    geos = [hats(tiny_geometry(seed=317 + i, rays=(12000, 1500, 1000), n_r=16, n_phi=24, n_frames=134 + i), 100) for i in range(2)]
+    launches_and_bits(gpu_lib, geos, (8,), 2)
