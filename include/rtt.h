@@ -35,7 +35,9 @@
  *  - The ratio dt_obs/dt_src must be a rational P/Q with Q <= 64, P <= 4096.
  *  - Scratch that a driver allocates comes from a pool of idle device blocks
  *    (at most 8 GiB idle per GPU), which go back to the device when an
- *    allocation fails and when the last geometry handle is freed.
+ *    allocation of a driver's scratch fails and when the last geometry handle
+ *    is freed.  Until then they are reserved against the caller's own
+ *    allocations; scratch_trim gives them back at once.
  */
 #ifndef RTT_H
 #define RTT_H
@@ -208,6 +210,14 @@ int op_apply_shared(const rtt_geometry* geom, const float* x, float* y, int32_t 
  */
 int op_apply_adjoint(const rtt_geometry* geom, const float* y, float* x, int32_t nvec,
                      uint32_t order_mask, void* stream);
+
+/*
+ * scratch_trim -- give every idle block of the library's scratch (on every
+ * GPU) back to the device; *freed (nullable) receives their bytes.  Scratch in
+ * use, factors and handles are untouched.  Waits for the device, as freeing
+ * memory does; never fails.
+ */
+int scratch_trim(int64_t* freed);
 
 /* ------------------------------------------------------------------ spectra */
 enum { RTT_SVD_RSVD = 0, RTT_SVD_BLOCK_LANCZOS = 1 };

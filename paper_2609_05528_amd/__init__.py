@@ -27,7 +27,7 @@ EXPORTED = ("geometry_load", "geometry_free", "geometry_info", "geometry_member"
             "svd_converged", "tsvd_solve", "ridge_solve", "mixer_create", "mixer_free", "mixer_info", "mixer_member", "mixer_set_variant",
             "mix_apply", "mix_apply_noalloc", "mix_adjoint", "mix_covariance", "reference_response", "age_information", "age_window",
             "age_reach", "age_window_error", "tsvd_project", "noise_add", "synthesis_create", "synthesis_free",
-            "synthesis_info", "synth_expand", "synth_project", "synthesis_audit", "age_fisher", "last_error")
+            "synthesis_info", "synth_expand", "synth_project", "synthesis_audit", "age_fisher", "scratch_trim", "last_error")
 
 
 class RttError(RuntimeError):
@@ -154,6 +154,7 @@ def require_native():
         "synth_project": [vp, vp, vp, i32, vp],
         "synthesis_audit": [vp, vp, u32, vp, vp, vp],
         "age_fisher": [vp, vp, _dp, i32, ctypes.c_double, u32, _dp, vp],
+        "scratch_trim": [ctypes.POINTER(ctypes.c_int64)],
     }
     for name, args in sig.items():
         fn = getattr(lib, name)
@@ -313,6 +314,13 @@ def variant_names(adjoint: bool):
 
 def geometry_load(geoms, sigma_omega=0.0, drop_invalid=False) -> Geometry:
     return Geometry(geoms, sigma_omega=sigma_omega, drop_invalid=drop_invalid)
+
+
+def scratch_trim() -> int:
+    """Give the idle scratch that the library keeps between calls back to the device; returns its bytes."""
+    n = ctypes.c_int64()
+    _check(require_native().scratch_trim(ctypes.byref(n)))
+    return n.value
 
 
 def _nvec(t, n):

@@ -594,8 +594,8 @@ __global__ void k_scale_inv_sq(const double* __restrict__ Cd, const double* __re
 // rSVD on a fresh process and 110 ms of it (37 of 60 ms for a block Lanczos run) once the process had
 // allocated and returned tens of GB.  Blocks come back only after a device synchronisation (what hipFree
 // does too), so whoever takes one next, on any thread or stream, finds it unused.  At most POOL_IDLE_MAX
-// bytes per GPU stay idle, the longest idle leave first, all of them when an allocation fails or the
-// last geometry handle is freed.
+// bytes per GPU stay idle, the longest idle leave first, all of them when an allocation fails, the caller asks
+// (scratch_trim) or the last geometry handle is freed.
 namespace {
 constexpr size_t POOL_IDLE_MAX = (size_t)8 << 30;
 struct IdleBlock {
@@ -613,11 +613,13 @@ Pool& pool()
     static Pool* p = new Pool();   // never destroyed: the runtime may be gone before static destructors run
     return *p;
 }
-// frees idle blocks of a device (or all) until at most `keep` bytes of it stay; the lock is held
-void pool_trim(Pool& q, int dev, size_t keep)
+// frees idle blocks of a device (or all) until at most `keep` bytes of it stay, and returns the bytes freed;
+// the lock is held
+size_t pool_trim(Pool& q, int dev, size_t keep)
 {
     size_t held = 0;
     for (const IdleBlock& b : q.idle) held += (dev < 0 || b.dev == dev) ? b.cap : 0;
+    const size_t before = held;
     for (auto it = q.idle.begin(); it != q.idle.end() && held > keep;) {
         if (dev >= 0 && it->dev != dev) {
             ++it;
@@ -627,6 +629,7 @@ void pool_trim(Pool& q, int dev, size_t keep)
         held -= it->cap;
         it = q.idle.erase(it);
     }
+    return before - held;
 }
 }  // namespace
 
@@ -920,3 +923,13 @@ int dots(Workspace& ws, const float* a, int64_t lda, const float* b, int64_t ldb
 }
 
 }  // namespace rtt
+
+extern "C" int scratch_trim(int64_t* freed)
+{
+    using namespace rtt;
+    Pool& q = pool();
+    std::lock_guard<std::mutex> lock(q.m);
+    const size_t n = pool_trim(q, -1, 0);
+    if (freed) *freed = (int64_t)n;
+    return RTT_OK;
+}

@@ -1,0 +1,61 @@
+"""The pool of idle scratch: what stays in it, how much, and who gets it back."""
+import gc
+
+import numpy as np
+import pytest
+
+from test_gpu_operator import say
+from tinygeo import tiny_geometry
+
+pytestmark = pytest.mark.gpu
+GIB = 1 << 30
+
+
+def free_bytes():
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def large_geometry():
+    """About 3.3M data rows: the blocks of a rank-256 rSVD (288 vectors) are 3.8 GB each."""
+    return tiny_geometry(seed=330, rays=(20000, 3000, 2800), n_r=16, n_phi=24, n_frames=128)
+
+
+def test_idle_scratch_is_bounded_and_given_back_on_request(gpu_lib):
+    rtt = gpu_lib
+    G = rtt.Geometry(large_geometry())
+    rtt.scratch_trim()
+    before = free_bytes()
+    rtt.rsvd(G, k=256, p=32, q=0)      # Y and Y2 alone are 7.6 GB; the pool keeps what fits its bound
+    held = before - free_bytes()
+    say("case idle scratch", held)
+    assert GIB < held <= 8 * GIB
+    assert rtt.scratch_trim() >= held - (64 << 20)
+    assert rtt.scratch_trim() == 0
+    assert before - free_bytes() <= 64 << 20
+    # a block that does not fit beside what is idle sends the longest idle ones away
+    for k in (64, 128, 192, 224, 256):
+        rtt.rsvd(G, k=k, p=32, q=0)
+        assert before - free_bytes() <= 8 * GIB, k
+    rtt.scratch_trim()
+
+
+def test_idle_scratch_returns_with_the_last_handle(gpu_lib):
+    rtt = gpu_lib
+    gc.collect()
+    alive = [o for o in gc.get_objects() if type(o) is rtt.Geometry and getattr(o, "_h", None) is not None]
+    if alive:
+        pytest.skip("%d handles of other tests are alive" % len(alive))
+    G, H = rtt.Geometry(large_geometry()), rtt.Geometry(tiny_geometry(seed=331))
+    rtt.scratch_trim()
+    before = free_bytes()
+    rtt.rsvd(G, k=64, p=32, q=0)
+    held = before - free_bytes()
+    H.free()
+    assert held > GIB and before - free_bytes() >= held - (64 << 20)   # G is alive
+    G.free()
+    say("case last handle", held)
+    assert free_bytes() >= before
+    assert rtt.scratch_trim() == 0
