@@ -35,8 +35,8 @@
  *  - The ratio dt_obs/dt_src must be a rational P/Q with Q <= 64, P <= 4096.
  *  - Scratch that a driver allocates comes from a pool of idle device blocks
  *    (at most 8 GiB idle per GPU), which go back to the device when an
- *    allocation of a driver's scratch fails and when the last geometry handle
- *    is freed.  Until then they are reserved against the caller's own
+ *    allocation of this library fails and when the last geometry handle is
+ *    freed.  Until then they are reserved against the caller's own
  *    allocations; scratch_trim gives them back at once.
  */
 #ifndef RTT_H

@@ -594,7 +594,7 @@ __global__ void k_scale_inv_sq(const double* __restrict__ Cd, const double* __re
 // rSVD on a fresh process and 110 ms of it (37 of 60 ms for a block Lanczos run) once the process had
 // allocated and returned tens of GB.  Blocks come back only after a device synchronisation (what hipFree
 // does too), so whoever takes one next, on any thread or stream, finds it unused.  At most POOL_IDLE_MAX
-// bytes per GPU stay idle, the longest idle leave first, all of them when an allocation fails, the caller asks
+// bytes per GPU stay idle, the longest idle leave first, all of them when an allocation of this library fails, the caller asks
 // (scratch_trim) or the last geometry handle is freed.
 namespace {
 constexpr size_t POOL_IDLE_MAX = (size_t)8 << 30;
@@ -641,6 +641,27 @@ void pool_user(int change)
     if (q.users <= 0) pool_trim(q, -1, 0);
 }
 
+hipError_t dev_malloc(void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        int dev = -1;
+        (void)hipGetDevice(&dev);
+        {
+            Pool& q = pool();
+            std::lock_guard<std::mutex> lock(q.m);
+            pool_trim(q, dev, 0);
+        }
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
 DevBlock dev_take(size_t bytes)
 {
     // sizes in steps that let a later call of about the same size reuse the block
@@ -663,21 +684,7 @@ DevBlock dev_take(size_t bytes)
             return r;
         }
     }
-    hipError_t e = hipMalloc(&r.p, want);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lock(q.m);
-            pool_trim(q, r.dev, 0);
-        }
-        e = hipMalloc(&r.p, want);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        r.p = nullptr;
-        return r;
-    }
-    r.cap = want;
+    if (dev_malloc(&r.p, want) == hipSuccess) r.cap = want;
     return r;
 }
 

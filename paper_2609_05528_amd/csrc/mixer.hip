@@ -439,7 +439,7 @@ extern "C" int mixer_create(const rtt_geometry* g, int32_t kind, const int64_t* 
     hipError_t e = hipSetDevice(m->device);
     auto up = [&](int64_t** dst, const std::vector<int64_t>& v) {
         if (e != hipSuccess || v.empty()) return;
-        e = hipMalloc((void**)dst, v.size() * sizeof(int64_t));
+        e = dev_malloc((void**)dst, v.size() * sizeof(int64_t));
         if (e == hipSuccess) e = hipMemcpy(*dst, v.data(), v.size() * sizeof(int64_t), hipMemcpyHostToDevice);
     };
     up(&m->d_chunk, chunk);

@@ -102,6 +102,9 @@ struct Member {
 
 struct Workspace;
 void pool_user(int change);   // a geometry handle is made (+1) or freed (-1): see the scratch pool in dense.hip
+// hipMalloc for every device allocation of the library: without memory left, the current device's idle scratch goes
+// back first.  On failure *p is NULL and no error is left behind.
+hipError_t dev_malloc(void** p, size_t bytes);
 
 }  // namespace rtt
 

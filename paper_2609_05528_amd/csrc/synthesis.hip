@@ -500,10 +500,10 @@ extern "C" int synthesis_create(const rtt_geometry* g, int32_t gi, const rtt_syn
     s->device = g->device;
     hipError_t e = hipSetDevice(s->device);
     double *dR = nullptr, *dP = nullptr, *dT = nullptr;
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_Q, sizeof(float) * (size_t)d * m.n_cols);
-    if (e == hipSuccess) e = hipMalloc((void**)&dR, sizeof(double) * R.size());
-    if (e == hipSuccess) e = hipMalloc((void**)&dP, sizeof(double) * P.size());
-    if (e == hipSuccess) e = hipMalloc((void**)&dT, sizeof(double) * T.size());
+    if (e == hipSuccess) e = dev_malloc((void**)&s->d_Q, sizeof(float) * (size_t)d * m.n_cols);
+    if (e == hipSuccess) e = dev_malloc((void**)&dR, sizeof(double) * R.size());
+    if (e == hipSuccess) e = dev_malloc((void**)&dP, sizeof(double) * P.size());
+    if (e == hipSuccess) e = dev_malloc((void**)&dT, sizeof(double) * T.size());
     if (e == hipSuccess) e = hipMemcpy(dR, R.data(), sizeof(double) * R.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dP, P.data(), sizeof(double) * P.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dT, T.data(), sizeof(double) * T.size(), hipMemcpyHostToDevice);
@@ -524,7 +524,7 @@ extern "C" int synthesis_create(const rtt_geometry* g, int32_t gi, const rtt_syn
         std::vector<float> fR(R.begin(), R.end()), fP(P.begin(), P.end()), fT(T.begin(), T.end());
         auto up = [&](float** dst, const std::vector<float>& h) {
             if (e != hipSuccess) return;
-            e = hipMalloc((void**)dst, sizeof(float) * h.size());
+            e = dev_malloc((void**)dst, sizeof(float) * h.size());
             if (e == hipSuccess) e = hipMemcpy(*dst, h.data(), sizeof(float) * h.size(), hipMemcpyHostToDevice);
         };
         up(&s->d_R, fR);

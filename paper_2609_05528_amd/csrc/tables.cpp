@@ -434,16 +434,16 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
     hipGetDevice(&h->device);
     size_t rb = recs.size() * sizeof(RayRec), cb = cstart.size() * sizeof(int32_t);
     size_t vb = std::max<size_t>(visits.size(), 1) * sizeof(Visit), tb = vtask.size() * sizeof(int64_t);
-    hipError_t e = hipMalloc((void**)&h->d_rays, rb);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_cell_start, cb);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_visits, vb);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_vtask, tb);
+    hipError_t e = dev_malloc((void**)&h->d_rays, rb);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_cell_start, cb);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_visits, vb);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_vtask, tb);
     const size_t fb = fwd.size() * sizeof(FwdRec);
     fwd.resize(fwd.size() + FWD_PAD, FwdRec{});
     const size_t fpad = FWD_PAD * sizeof(FwdRec);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd, fb + fpad);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_fwd, fb + fpad);
     if (e == hipSuccess) e = hipMemcpy(h->d_fwd, fwd.data(), fb + fpad, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_fwd_row, fb);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_fwd_row, fb);
     if (e == hipSuccess) e = hipMemcpy(h->d_fwd_row, fwd_row.data(), fb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_rays, recs.data(), rb, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->d_cell_start, cstart.data(), cb, hipMemcpyHostToDevice);
@@ -455,7 +455,7 @@ extern "C" int geometry_load(const rtt_grid* grids, const rtt_raymap* maps, int3
     for (const Member& m : h->members) seg.insert(seg.end(), {m.col_offset, m.n_cols});
     for (const Member& m : h->members) seg.insert(seg.end(), {m.row_offset, m.n_rows});
     const size_t sb = seg.size() * sizeof(int64_t);
-    if (e == hipSuccess) e = hipMalloc((void**)&h->d_seg, sb);
+    if (e == hipSuccess) e = dev_malloc((void**)&h->d_seg, sb);
     if (e == hipSuccess) e = hipMemcpy(h->d_seg, seg.data(), sb, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         int rc = hip_fail(e, "geometry_load upload");

@@ -59,3 +59,36 @@ def test_idle_scratch_returns_with_the_last_handle(gpu_lib):
     say("case last handle", held)
     assert free_bytes() >= before
     assert rtt.scratch_trim() == 0
+
+
+def fill_device(leave):
+    """Tensors that leave about `leave` bytes of the device free."""
+    import torch
+    kept = []
+    for piece in (8 * GIB, GIB, 64 << 20):
+        while torch.cuda.mem_get_info()[0] > leave + piece:
+            kept.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+    return kept
+
+
+@pytest.mark.parametrize("what", ["geometry", "synthesis"])
+def test_a_handle_that_needs_the_idle_memory_gets_it(gpu_lib, what):
+    """Drivers freed their scratch on return before it was pooled: what fitted beside them then must fit now."""
+    rtt = gpu_lib
+    G = rtt.Geometry(large_geometry())
+    S = rtt.Geometry(tiny_geometry(seed=332, n_r=64, n_phi=64, n_frames=240))
+    big = tiny_geometry(seed=333, rays=(3000000,), n_r=64, n_phi=64, n_frames=1)     # about 1 GB of tables
+    rtt.scratch_trim()
+    rtt.rsvd(G, k=256, p=32, q=0)
+    kept = fill_device(384 << 20)
+    say("case full device", what, len(kept), S.n_cols)
+    try:
+        if what == "geometry":
+            made = rtt.Geometry(big)
+            assert made.table_bytes > (384 << 20) + (64 << 20)
+        else:
+            made = rtt.Synthesis(S, n_radial=8, m_max=4, n_temporal=8)                # 576 columns of Q, 2.4 GB
+        made.free()
+    finally:
+        del kept
+        rtt.scratch_trim()
