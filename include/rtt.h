@@ -38,6 +38,10 @@
  *    allocation of this library fails and when the last geometry handle is
  *    freed.  Until then they are reserved against the caller's own
  *    allocations; scratch_trim gives them back at once.
+ *  - Scratch that a handle keeps (tsvd_solve, asynchronous ridge_solve, mix_*,
+ *    synth_*) grows by being replaced: a call that needs more of it than any
+ *    earlier one on that handle invalidates the graphs captured from calls on
+ *    the handle before.
  */
 #ifndef RTT_H
 #define RTT_H

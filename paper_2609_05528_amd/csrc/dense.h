@@ -22,9 +22,13 @@ struct DevBlock {
 DevBlock dev_take(size_t bytes);
 void dev_give(const std::vector<DevBlock>& blocks);   // blocks of one device
 
-// Named, grow-only device scratch buffers owned by one driver call.
+// Named, grow-only device scratch buffers owned by one driver call, or by a handle.  A buffer that a handle
+// outgrows goes back to the device, not to the idle blocks: a graph captured before may still name it, and would
+// write into whatever driver got it next.
 struct Workspace {
     std::map<std::string, DevBlock> bufs;
+    const bool of_handle;
+    explicit Workspace(bool of_handle_ = false) : of_handle(of_handle_) {}
     void* get(const char* name, size_t bytes);
     void release();
     ~Workspace();

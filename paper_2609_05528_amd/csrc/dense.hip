@@ -697,6 +697,7 @@ void dev_give(const std::vector<DevBlock>& blocks)
     (void)hipGetDevice(&cur);
     if (cur != dev) (void)hipSetDevice(dev);
     const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
     Pool& q = pool();
     {
         std::lock_guard<std::mutex> lock(q.m);
@@ -723,7 +724,8 @@ void* Workspace::get(const char* name, size_t bytes)
     auto it = bufs.find(name);
     if (it != bufs.end() && it->second.cap >= bytes) return it->second.p;
     if (it != bufs.end()) {
-        dev_give({it->second});
+        if (of_handle) (void)hipFree(it->second.p);
+        else dev_give({it->second});
         bufs.erase(it);
     }
     const DevBlock b = dev_take(bytes);

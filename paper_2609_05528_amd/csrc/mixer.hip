@@ -52,7 +52,7 @@ struct rtt_mixer {
     int64_t* d_src = nullptr;      // [n_src][4]: source row offset, mixed row offset, frames word, 0
     int32_t vb_apply = 0, vb_adjoint = 0;   // pinned vectors per wave (0: chosen per call)
     int device = 0;
-    mutable rtt::Workspace ws;
+    mutable rtt::Workspace ws{true};
     uint32_t magic = rtt::MIX_MAGIC;
 };
 

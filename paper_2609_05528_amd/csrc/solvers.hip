@@ -197,7 +197,7 @@ extern "C" int ridge_solve(const rtt_geometry* g, const float* y, int32_t nrhs, 
     int64_t max_cols = 0;
     for (const Member& mb : g->members) max_cols = std::max(max_cols, mb.n_cols);
     Workspace local;
-    if (async && !g->solve_ws) g->solve_ws = new (std::nothrow) Workspace();
+    if (async && !g->solve_ws) g->solve_ws = new (std::nothrow) Workspace(true);
     Workspace& ws = async ? *g->solve_ws : local;
     if (async && !g->solve_ws) return fail(RTT_ENOMEM, "ridge_solve workspace");
     float* r = (float*)ws.get("cg_r", sizeof(float) * (size_t)nrhs * n);

@@ -507,7 +507,7 @@ static int tsvd_apply(const rtt_geometry* g, const rtt_svd* sv, const float* y, 
     const int64_t n = sv->n_cols;
     int rc;
     if (tt == 0) return fill(x, (int64_t)nrhs * n, 0.f, s);
-    if (!sv->ws) const_cast<rtt_svd*>(sv)->ws = new (std::nothrow) Workspace();
+    if (!sv->ws) const_cast<rtt_svd*>(sv)->ws = new (std::nothrow) Workspace(true);
     if (!sv->ws) return fail(RTT_ENOMEM, "tsvd workspace");
     Workspace& ws = *sv->ws;
     const int sets = sv->sets;

@@ -37,7 +37,7 @@ struct rtt_synthesis {
     int32_t n_r = 0, n_phi = 0, K = 0;
     bool separable = false;   // the factor-by-factor kernels fit their LDS limits
     int device = 0;
-    mutable rtt::Workspace ws;
+    mutable rtt::Workspace ws{true};
     uint32_t magic = rtt::SYN_MAGIC;
 };
 

@@ -92,3 +92,28 @@ def test_a_handle_that_needs_the_idle_memory_gets_it(gpu_lib, what):
     finally:
         del kept
         rtt.scratch_trim()
+
+
+def test_scratch_that_a_handle_outgrows_is_not_handed_to_other_calls(gpu_lib):
+    """A graph captured from a call on the handle still names the old buffers: no other driver may get them."""
+    import torch
+    rtt = gpu_lib
+    geo = tiny_geometry(seed=334, rays=(900, 90, 60), n_r=12, n_phi=16, n_frames=64)
+    G = rtt.Geometry(geo)
+    sv = rtt.rsvd(G, k=48, p=16, q=0, seed=1)
+    M = rtt.Mixer(G, "total_flux")
+    S = rtt.Synthesis(G, n_radial=4, m_max=3, n_temporal=8)
+    calls = {
+        "ridge": lambda n: rtt.ridge_solve(G, torch.ones((n, G.n_rows), device="cuda"), 1.0, maxit=2, async_mode=True),
+        "tsvd": lambda n: rtt.tsvd_solve(G, sv, torch.ones((n, G.n_rows), device="cuda"), t=40),
+        "mixer": lambda n: rtt.mix_apply(M, torch.ones((n, G.n_rows), device="cuda")),
+        "synthesis": lambda n: S.project(torch.ones((n, G.n_cols), device="cuda")),
+    }
+    for name, call in calls.items():
+        call(3)
+        rtt.scratch_trim()
+        call(40)
+        call(90)
+        torch.cuda.synchronize()
+        say("case outgrown", name)
+        assert rtt.scratch_trim() == 0, name
