@@ -2701,6 +2701,14 @@ static bool apply_group(const rtt_geometry* g, int b, int e, int nvec, int* vari
 // loads need no more), so that a block gives the same bits wherever it starts
 static bool cells_rows_ok(const Member& m) { return (m.Q == 1 || m.grid.n_frames % 2 == 0) && adjoint_cells_ok(m); }
 
+// One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
+// 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
+// 240 against 248), which need even rows at half steps.
+bool adjoint_by_cells(const Member& m)
+{
+    return 2 * m.n_rays >= 9 * (int64_t)(m.grid.n_r - 1) * m.grid.n_phi && cells_rows_ok(m);
+}
+
 int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
 {
     if (m.adj_variant >= 0) return m.adj_variant;
@@ -2709,11 +2717,7 @@ int adjoint_variant_for(const rtt_geometry* g, const Member& m, int nvec)
     // 2.54 ms for base cells member by member; 8 vectors 460 against 394 us; one vector without row pairs
     // 170 against 227 us with them).  For one launch of several of them see adjoint_group.
     if (g->members.size() > 1) return g->pair_tasks * ((nvec + 1) / 2) >= 4096 ? 19 : 16;
-    // One geometry: the base cells from 4.5 rays a cell on (one vector: 3.5 rays a cell 10.2 against 11.7 us,
-    // 5.1 11.3 against 16.2, 46 22 against 78; 60 vectors: 3.5 164 against 151 us, 5.1 200 against 198, 7.0
-    // 240 against 248), which need even rows at half steps.
-    const int64_t cells = (int64_t)(m.grid.n_r - 1) * m.grid.n_phi;
-    if (2 * m.n_rays >= 9 * cells && cells_rows_ok(m)) return 23;
+    if (adjoint_by_cells(m)) return 23;
     // Odd rows at half steps have no aligned frame pairs: one vector per wave (89 frames, 12 vectors: 50 us
     // against 55 with two and 82 with four; 107 frames, 161 vectors: 242, 259, 267).
     if (m.Q == 2 && m.grid.n_frames % 2) return 16;

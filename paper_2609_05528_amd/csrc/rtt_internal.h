@@ -156,6 +156,7 @@ int launch_adjoint(const rtt_geometry* g, const Member& m, const float* y, float
                    int64_t y_stride, int64_t x_stride, uint32_t mask, hipStream_t s, int variant);
 // A^T over base cells (adjoint_cells.hip); data rows must be even when Q = 2
 bool adjoint_cells_ok(const Member& m);
+bool adjoint_by_cells(const Member& m);   // a lone unpinned member takes it
 int launch_adjoint_cells(const rtt_geometry* g, const Member& m, const float* y, float* x, int nvec, int64_t y_stride,
                          int64_t x_stride, uint32_t mask, hipStream_t s, float* x2 = nullptr);
 int n_adjoint_variants();

@@ -237,9 +237,9 @@ extern "C" int ridge_solve(const rtt_geometry* g, const float* y, int32_t nrhs, 
     // Where A^T goes by base cells its two launches, the second of which adds to the first, become one that
     // leaves two shares, and the kernel that follows adds them (256^2, one right-hand side: 24.4 -> 15.1 us a
     // product, 20 iterations 1002 -> 814 us).
-    // (The buffer does not depend on the variant of the moment: a captured solve finds it whatever is pinned.)
+    // (The buffer depends on the geometry, not on the variant of the moment: a captured solve finds it whatever is pinned.)
     float* Ap2 = nullptr;
-    if (G == 1 && adjoint_cells_ok(g->members[0])) Ap2 = (float*)ws.get("cg_ap2", sizeof(float) * (size_t)nrhs * n);
+    if (G == 1 && adjoint_by_cells(g->members[0])) Ap2 = (float*)ws.get("cg_ap2", sizeof(float) * (size_t)nrhs * n);
     bool parts2 = Ap2 != nullptr;
     if (parts2 && (rc = fill(Ap2, (int64_t)nrhs * n, 0.f, s))) return rc;
     while (it < maxit) {

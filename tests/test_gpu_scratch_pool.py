@@ -92,6 +92,7 @@ def test_a_handle_that_needs_the_idle_memory_gets_it(gpu_lib, what):
     finally:
         del kept
         rtt.scratch_trim()
+        free_bytes()       # torch's cache goes back to the device too
 
 
 def test_scratch_that_a_handle_outgrows_is_not_handed_to_other_calls(gpu_lib):
@@ -117,3 +118,20 @@ def test_scratch_that_a_handle_outgrows_is_not_handed_to_other_calls(gpu_lib):
         torch.cuda.synchronize()
         say("case outgrown", name)
         assert rtt.scratch_trim() == 0, name
+
+
+@pytest.mark.parametrize("rays,blocks", [((300, 40, 20), 3), ((4000, 400, 300), 4)])
+def test_ridge_keeps_a_second_share_of_the_adjoint_only_where_it_uses_it(gpu_lib, rays, blocks):
+    """Scratch of a solve: the residual, the direction and A^T A p, a data block, and a second share of A^T A p
+    where the adjoint goes by base cells (from 4.5 rays a cell on)."""
+    import torch
+    rtt = gpu_lib
+    geo = tiny_geometry(seed=335, rays=rays, n_r=16, n_phi=24, n_frames=64)
+    G = rtt.Geometry(geo)
+    nrhs = 512
+    Y = torch.ones((nrhs, G.n_rows), device="cuda")
+    rtt.scratch_trim()
+    rtt.ridge_solve(G, Y, 1.0, maxit=1, raise_on_noconv=False)
+    used = rtt.scratch_trim()
+    say("case ridge scratch", used, 4 * nrhs * G.n_cols)
+    assert blocks * 4 * nrhs * G.n_cols <= used - 4 * nrhs * G.n_rows < (blocks + 0.5) * 4 * nrhs * G.n_cols
