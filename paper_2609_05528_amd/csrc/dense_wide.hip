@@ -352,7 +352,6 @@ void gram_split(const float* Y, int64_t ld, int M, int64_t L, int64_t slice, int
 {
     const bool vl = (((uintptr_t)Y) & 15) == 0 && (ld % 4) == 0;
     switch (M / 32) {
-    case 1: gram_t<1>(Y, ld, L, slice, nsplit, vl, part, run_if, s); break;
     case 2: gram_t<2>(Y, ld, L, slice, nsplit, vl, part, run_if, s); break;
     case 3: gram_t<3>(Y, ld, L, slice, nsplit, vl, part, run_if, s); break;
     case 4: gram_t<4>(Y, ld, L, slice, nsplit, vl, part, run_if, s); break;

@@ -1106,10 +1106,12 @@ constexpr int ABS_KMAX = 2 * WAVE;
 // vector (x, y already offset to the member's blocks), every frame.
 // STAGE (records in data-row order, Q = 1): NB rays that are consecutive data rows with rows of at
 // most lean_fcmax(1) frames leave as one staged, 16-byte aligned range (as lean4r).
+// VEC4 (Q = 2): rows of a multiple of 4 frames, 16-byte aligned (Q = 1 stores four frames at any start).
 template <int Q, int NB, bool VEC4, bool REUSE, bool STAGE = false>
 __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restrict__ x, float* __restrict__ y,
                                          int64_t blk)
 {
+    static_assert(Q == 2 || !VEC4, "Q = 1 has one form");
     float(*zs_all)[NB][LEAN_ZS] = lean_lds<NB>();
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = threadIdx.x >> 6;
@@ -1244,7 +1246,7 @@ __device__ __forceinline__ void abs_body(const LeanArgs& a, const float* __restr
         const float th = rc[j].th0;
         const int k0 = rc[j].k0;
         float* yr = y + (int64_t)rc[j].row * F;
-        if (VEC4 && Q == 2) {
+        if (VEC4) {
             const bool c1 = th >= 0.5f;
             const float th1 = c1 ? th - 0.5f : th + 0.5f;
             for (int g = lane; 4 * g < F; g += WAVE) {
@@ -1366,10 +1368,13 @@ __global__ __launch_bounds__(A_WAVES * WAVE) void k_apply_abs_multi(LeanMulti a)
         la.fc = mm.fc;
         const float* xv = a.x + (int64_t)v * a.x_stride + mm.x_off;
         float* yv = a.y + (int64_t)v * a.y_stride + mm.y_off;
-        if (VEC4 && mm.wide)
-            abs_body<Q, 4, true, true>(la, xv, yv, (int64_t)b);
-        else
-            abs_body<Q, 4, false, true>(la, xv, yv, (int64_t)b);
+        if constexpr (VEC4) {
+            if (mm.wide) {
+                abs_body<Q, 4, true, true>(la, xv, yv, (int64_t)b);
+                continue;
+            }
+        }
+        abs_body<Q, 4, false, true>(la, xv, yv, (int64_t)b);
     }
 }
 
@@ -2933,27 +2938,21 @@ int launch_apply(const rtt_geometry* g, const Member& m, const float* x, float* 
         la.x_bytes = (int)(m.n_cols * 4);
         la.mask = mask;
         la.fc = m.grid.n_frames;
-        const int wa = m.Q == 1 ? 2 : 4;
-        const bool vec4 = (la.F % wa) == 0 && (((uintptr_t)y) & (4 * wa - 1)) == 0 && (nvec == 1 || (y_stride % wa) == 0);
+        const bool vec4 = (la.F % 4) == 0 && (((uintptr_t)y) & 15) == 0 && (nvec == 1 || (y_stride % 4) == 0);
         const int nb = variant == 12 ? 8 : 4;
         const dim3 grid((unsigned)((la.n_rays + (int64_t)A_WAVES * nb - 1) / ((int64_t)A_WAVES * nb)), (unsigned)nvec);
         const dim3 blk(A_WAVES * WAVE);
-#define RTT_ABS(Q_, NB_)                                                                      \
-    do {                                                                                      \
-        if (vec4) hipLaunchKernelGGL((k_apply_abs<Q_, NB_, true>), grid, blk, 0, s, la);      \
-        else hipLaunchKernelGGL((k_apply_abs<Q_, NB_, false>), grid, blk, 0, s, la);          \
-    } while (0)
-        if (variant == 14 && m.Q == 1) {
-            if (vec4) hipLaunchKernelGGL((k_apply_abs<1, 4, true, true>), grid, blk, 0, s, la);
-            else hipLaunchKernelGGL((k_apply_abs<1, 4, false, true>), grid, blk, 0, s, la);
-        } else if (m.Q == 1) {
-            if (nb == 4) RTT_ABS(1, 4);
-            else RTT_ABS(1, 8);
+        if (m.Q == 1) {
+            if (variant == 14) hipLaunchKernelGGL((k_apply_abs<1, 4, false, true>), grid, blk, 0, s, la);
+            else if (nb == 4) hipLaunchKernelGGL((k_apply_abs<1, 4, false>), grid, blk, 0, s, la);
+            else hipLaunchKernelGGL((k_apply_abs<1, 8, false>), grid, blk, 0, s, la);
+        } else if (nb == 4) {
+            if (vec4) hipLaunchKernelGGL((k_apply_abs<2, 4, true>), grid, blk, 0, s, la);
+            else hipLaunchKernelGGL((k_apply_abs<2, 4, false>), grid, blk, 0, s, la);
         } else {
-            if (nb == 4) RTT_ABS(2, 4);
-            else RTT_ABS(2, 8);
+            if (vec4) hipLaunchKernelGGL((k_apply_abs<2, 8, true>), grid, blk, 0, s, la);
+            else hipLaunchKernelGGL((k_apply_abs<2, 8, false>), grid, blk, 0, s, la);
         }
-#undef RTT_ABS
         RTT_HIP(hipGetLastError());
         return RTT_OK;
     }
@@ -3361,8 +3360,7 @@ static bool apply_multi(const rtt_geometry* g, int b, int e, const float* x, flo
     const dim3 grid(multi_grid(a.total, persist)), blk(A_WAVES * WAVE);
     if (use_abs) {
         if (m0.Q == 1) {
-            if (vec4) hipLaunchKernelGGL((k_apply_abs_multi<1, true>), grid, blk, 0, s, a);
-            else hipLaunchKernelGGL((k_apply_abs_multi<1, false>), grid, blk, 0, s, a);
+            hipLaunchKernelGGL((k_apply_abs_multi<1, false>), grid, blk, 0, s, a);
         } else {
             if (vec4) hipLaunchKernelGGL((k_apply_abs_multi<2, true>), grid, blk, 0, s, a);
             else hipLaunchKernelGGL((k_apply_abs_multi<2, false>), grid, blk, 0, s, a);
