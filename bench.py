@@ -31,9 +31,8 @@ sys.path.insert(0, ROOT)
 METRIC = "A+A^T applies/sec and HBM GB/s; batched vs plain at 1e-5 rel err"
 HBM_PEAK_GBPS = 8000.0
 RAY_RECORD_BYTES = 32
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2609_05528_amd", "csrc", "operator.hip")
 # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (FETCH_SIZE scaled by 2.0,
-# the factor a 2 GiB plain copy reads; WRITE_SIZE by 1.0), valid only for the kernel source digest,
+# the factor a 2 GiB plain copy reads; WRITE_SIZE by 1.0), valid only for the operator's source digest,
 # workload, variant and launch modes they were taken on (see profiles/).
 MEASURED_TRAFFIC = {
     "op_apply_shared": [{"bytes": 10539672002, "digest": "3b624c25c4867114", "workload": "batch",
@@ -54,7 +53,7 @@ _tune_cache_copy = None
 
 def tune_cache():
     """The committed autotuner cache (written by paper_2609_05528_amd/make_tune_cache.py with many
-    repetitions) when it was made with the operator source this run uses: a private copy of it, so
+    repetitions) when it was made with the operator's sources this run uses: a private copy of it, so
     that every run -- profiled or not -- replays the same kernel choices.  None otherwise (every
     tune call then times the variants afresh)."""
     global _tune_cache_copy
@@ -63,15 +62,16 @@ def tune_cache():
     _tune_cache_copy = ""
     if os.path.exists(TUNE_CACHE):
         with open(TUNE_CACHE) as f:
-            head = f.readline().split()
-        if head[:2] == ["#", "operator"] and head[2:3] == [source_digest()]:
+            head = f.readline()
+        from paper_2609_05528_amd import build_lib
+        if head == build_lib.tune_cache_header():
             import tempfile
             fd, path = tempfile.mkstemp(prefix="rtt_tune_", suffix=".txt")
             with os.fdopen(fd, "w") as out, open(TUNE_CACHE) as src:
                 out.write(src.read())
             _tune_cache_copy = path
         else:
-            log("tune cache %s was made for another operator source: tuning afresh" % TUNE_CACHE)
+            log("tune cache %s was made for other operator sources: tuning afresh" % TUNE_CACHE)
     return _tune_cache_copy or None
 
 
@@ -84,9 +84,8 @@ def algorithmic_bytes(n_rows, n_cols, n_rays, n_cells, n_orders, nvec, adjoint):
 
 
 def source_digest():
-    import hashlib
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    from paper_2609_05528_amd import build_lib
+    return build_lib.operator_digest()
 
 
 def time_pair(torch, rtt, G, X, Y, XT, reps=10):

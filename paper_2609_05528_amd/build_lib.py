@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import glob
+import hashlib
 import os
 import subprocess
 import sys
@@ -26,6 +27,28 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-
 # the host FP64 kernels of the small SVD run on AVX2 + FMA (every EPYC has them); contraction stays
 # off, so every product and sum is rounded as in the plain build
 HOST_SIMD = {"smallla.cpp": ["-Xarch_host", "-march=x86-64-v3", "-Xarch_host", "-ffp-contract=off"]}
+
+
+# what decides the time of A and A^T and of their variants: the kernels, their records and the lists that
+# geometry_load builds for them
+OPERATOR_SOURCES = ("operator.hip", "adjoint_cells.hip", "rtt_internal.h", "tables.cpp")
+
+
+def operator_digest(csrc: str = CSRC) -> str:
+    """Digest of the operator's sources: timings and tuner choices taken with others are stale."""
+    h = hashlib.sha256()
+    for name in OPERATOR_SOURCES:
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(b"%s %d\n" % (name.encode(), os.fstat(f.fileno()).st_size))
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
+def tune_cache_header(csrc: str = CSRC) -> str:
+    """First line of a tuner cache made with these sources (the kernel file's own digest, then the digest of all)."""
+    with open(os.path.join(csrc, "operator.hip"), "rb") as f:
+        own = hashlib.sha256(f.read()).hexdigest()[:16]
+    return "# operator %s sources %s\n" % (own, operator_digest(csrc))
 
 
 def sources():

@@ -1,13 +1,12 @@
 """Write the autotuner cache that bench.py replays: the kernel variants and launch modes of the
 benchmark's workloads, timed with many repetitions on this GPU, under a header line naming the
-digest of the operator source they were timed with (bench.py ignores a cache whose digest does not
-match the source it runs, and then tunes afresh).
+digests of the operator's sources they were timed with (bench.py ignores a cache whose digests do
+not match the sources it runs, and then tunes afresh).
 
 Usage: python -m paper_2609_05528_amd.make_tune_cache [output path] [repetitions]
 """
 from __future__ import annotations
 
-import hashlib
 import os
 import sys
 
@@ -18,16 +17,12 @@ ROOT = os.path.dirname(HERE)
 DEFAULT = os.path.join(HERE, "tune_cache.txt")
 
 
-def operator_digest() -> str:
-    with open(os.path.join(HERE, "csrc", "operator.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
-
-
 def main():
     out = sys.argv[1] if len(sys.argv) > 1 else DEFAULT
     reps = int(sys.argv[2]) if len(sys.argv) > 2 else 9
     sys.path.insert(0, ROOT)
     import paper_2609_05528_amd as rtt
+    from paper_2609_05528_amd import build_lib
     import synth
     body = out + ".body"
     if os.path.exists(body):
@@ -44,7 +39,7 @@ def main():
     with open(body) as f:
         lines = f.read()
     with open(out, "w") as f:
-        f.write("# operator %s\n" % operator_digest())
+        f.write(build_lib.tune_cache_header())
         f.write(lines)
     os.remove(body)
     print("wrote", out)
