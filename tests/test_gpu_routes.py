@@ -166,3 +166,54 @@ def test_a_launch_mode_that_was_set_holds_for_large_geometries(gpu_lib):
     """8 vectors of about 8 MB a geometry go by one launch a geometry unless the caller asked for one."""
     geos = [hats(tiny_geometry(seed=317 + i, rays=(12000, 1500, 1000), n_r=16, n_phi=24, n_frames=134 + i), 100) for i in range(2)]
     launches_and_bits(gpu_lib, geos, (8,), 2)
+
+
+@pytest.mark.parametrize("name,geos,blocks", [
+    # one geometry, row sweep: one, two (2 .. 7), four vectors a wave on 64 rows (8 .. 31), row pairs from 8192 waves (128)
+    ("sweep", lambda: [tiny_geometry(seed=320, rays=(3000, 300, 200), n_r=64, n_phi=64, n_frames=33)], (1, 2, 7, 8, 31, 32, 127, 129)),
+    ("sweep half steps", lambda: [tiny_geometry(seed=321, rays=(3000, 300, 200), n_r=64, n_phi=64, n_frames=34, dt_obs=2.0)], (1, 2, 8, 32, 129)),
+    # half steps, more than 128 hats: records in row order up to 128 MiB of coefficients (60 vectors of 2.2 MB)
+    ("columns", lambda: [hats(tiny_geometry(seed=322, rays=(900, 90, 60), n_r=64, n_phi=64, n_frames=40, dt_obs=2.0), 136)], (1, 59, 60, 61)),
+    # several in one launch: row pairs from 2048 waves of short members (16 vectors), from 4096 of longer ones (31)
+    ("short members", lambda: [tiny_geometry(seed=323 + i, rays=(3000, 300, 200), n_r=32, n_phi=64, n_frames=33 + i) for i in range(4)], (1, 2, 15, 16, 17)),
+    ("longer members", lambda: [tiny_geometry(seed=327 + i, rays=(9000, 300, 200), n_r=32, n_phi=64, n_frames=33 + i) for i in range(4)], (1, 29, 30, 31, 32, 33)),
+])
+def test_blocks_on_both_sides_of_each_line_of_the_choice(gpu_lib, name, geos, blocks):
+    import torch
+    rtt = gpu_lib
+    geos = geos()
+    G = rtt.Geometry(geos)
+    nv = max(blocks) + 1
+    gen = torch.Generator("cuda").manual_seed(11)
+    X, Y = torch.rand((nv, G.n_cols), device="cuda", generator=gen), torch.randn((nv, G.n_rows), device="cuda", generator=gen)
+    y, x = rtt.op_apply(G, X), rtt.op_apply_adjoint(G, Y)
+    for geo, m in zip(geos, G.members):
+        cs, rs = slice(m["col_offset"], m["col_offset"] + m["n_cols"]), slice(m["row_offset"], m["row_offset"] + m["n_rows"])
+        assert rel(y[-1, rs].cpu().numpy(), oracle.forward(geo, X[-1, cs].double().cpu().numpy())) <= TOL
+        assert rel(x[-1, cs].cpu().numpy(), oracle.adjoint(geo, Y[-1, rs].double().cpu().numpy())) <= TOL
+    for n in blocks:
+        say("case lines", name, n)
+        assert torch.equal(rtt.op_apply(G, X[:n]), y[:n]), n
+        assert torch.equal(rtt.op_apply_adjoint(G, Y[:n]), x[:n]), n
+
+
+@pytest.mark.parametrize("n_hat", [8191, 8192, 8193])
+@pytest.mark.parametrize("late", [False, True])
+def test_age_windows_at_the_most_hats_they_take(gpu_lib, n_hat, late):
+    """8192 FP64 hats fill the 64 KB of LDS of a table's workgroup; one more goes by probes.  FP32 weights and
+    fractions enter a square, as in the other test of the windows: 2e-6 of the order's largest energy."""
+    rtt = gpu_lib
+    geo = hats(tiny_geometry(seed=331, rays=(50, 20), n_r=3, n_phi=4, n_frames=9), n_hat)
+    if late:   # the frames' origins at the other end of the hats
+        geo.grid = dataclasses.replace(geo.grid, s0=geo.grid.s0 - 4.0 * (n_hat - 12))
+    G = rtt.Geometry(geo)
+    ages = np.linspace(-8.0, 70.0, 9)
+    say("case age hats", n_hat, late)
+    E = rtt.age_information(G, ages, h=3.0)
+    Y = oracle.forward(geo, oracle.age_probes(geo.grid, ages, 3.0)).reshape(9, -1)
+    at = 0
+    for n, m in enumerate(geo.maps):
+        end = at + m.n_rays * 9
+        want = np.einsum("ar,ar->a", Y[:, at:end], Y[:, at:end])
+        assert np.max(want) > 0 and np.max(np.abs(E[:, 0, n] - want)) <= 2e-6 * np.max(want), n
+        at = end
