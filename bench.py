@@ -35,10 +35,10 @@ RAY_RECORD_BYTES = 32
 # the factor a 2 GiB plain copy reads; WRITE_SIZE by 1.0), valid only for the operator's source digest,
 # workload, variant and launch modes they were taken on (see profiles/).
 MEASURED_TRAFFIC = {
-    "op_apply_shared": [{"bytes": 10539672002, "digest": "3b624c25c4867114", "workload": "batch",
-                         "variant": ["abs4", "lean4", "lean4r", "reg1"], "modes": [2, 1]}],
-    "op_apply_adjoint": [{"bytes": 12563845017, "digest": "3b624c25c4867114", "workload": "batch",
-                          "variant": ["visitp2v"], "modes": [2, 1]}],
+    "op_apply_shared": [{"bytes": 10513073746, "digest": "386a7dd76f63e862", "workload": "batch",
+                         "variant": ["abs4", "abs4r", "lean4", "lean4r", "reg1"], "modes": [1, 1]}],
+    "op_apply_adjoint": [{"bytes": 12557622948, "digest": "386a7dd76f63e862", "workload": "batch",
+                          "variant": ["visitp2v"], "modes": [1, 1]}],
     "op_apply": [],
 }
 

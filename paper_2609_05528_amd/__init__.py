@@ -263,6 +263,7 @@ class Geometry:
     def set_batch_mode(self, apply=-1, adjoint=-1):
         """Launch mode of whole-operator calls on several geometries (0, 1, 2; see include/rtt.h)."""
         _check(require_native().geometry_set_batch_mode(self.handle, apply, adjoint))
+        self._read_members()   # the variants of a one-vector call
 
     @property
     def launches(self):

@@ -9,9 +9,9 @@
 // spreads a fragment's 16-byte reads over all banks), and each wave owns up to 7 tiles.  Every element is
 // read from memory once; the 64 x 64 blocks of the FP32 form read it 4.5 times.  (Parts below 2^-126 vanish,
 // so values below about 2^-110 lose relative accuracy; an infinity gives NaN.)
-// 288 vectors of 1.55M: 1.85 -> 1.03 ms, of which 0.01 the FP64 sum of the partials; rms error of the
-// normalised Gram matrix 1.6e-8 -> 3e-9.  The matrix cores are 40% busy, the waves wait for LDS fragments and
-// at the chunk barriers.
+// 288 vectors of 1.55M: 1.85 -> 1.03 ms alone with random rows (0.72 to 0.75 in an rSVD's trace), of which 0.01 the
+// FP64 sum of the partials; rms error of the normalised Gram matrix 1.6e-8 -> 3e-9.  The matrix cores are 59% busy
+// (rank-256 rSVD), the waves wait for LDS fragments and at the chunk barriers.
 //
 // combine_wide: Out = beta Out + C^T Y with FP32 matrix instructions.  A wave owns 32 columns and up to 9 row
 // blocks of Out; its columns of Y go from memory to registers, 16 rows two steps ahead, and C comes through
